@@ -407,6 +407,24 @@ keep_status stage_layer(keep_ctx* c, const keep_prompt* p, const PromptInfo& pi,
   return KEEP_OK;
 }
 
+// What the fused QKV epilogue reads and writes for one layer.
+QkvEpilogue qkv_epilogue(keep_ctx* c, const keep_layer_weights& w, const GemmB& b, const int32_t* row_pos,
+                         const int32_t* row_lo, void* k_cache_l, void* v_cache_l) {
+  QkvEpilogue qe{};
+  qe.row_pos = row_pos;
+  qe.row_lo = row_lo;
+  qe.rope_cos = c->rope_cos;
+  qe.rope_sin = c->rope_sin;
+  qe.bias[0] = w.bq; qe.bias[1] = w.bk; qe.bias[2] = w.bv;
+  qe.q = c->q;
+  qe.k_compact = c->kc;
+  qe.k_cache = k_cache_l;
+  qe.v_cache = v_cache_l;
+  qe.q_dim = b.n_rows[0];
+  qe.kv_dim = b.n_rows[1];
+  return qe;
+}
+
 // Steps of one layer on the compute stream, up to and including attention.
 template <typename T>
 keep_status layer_front(keep_ctx* c, const PromptInfo& pi, int layer, const LayerPlan& plan, const void* x_in,
@@ -441,18 +459,8 @@ keep_status layer_front(keep_ctx* c, const PromptInfo& pi, int layer, const Laye
   const int n_qkv = b.n_rows[0] + 2 * b.n_rows[1];
   if (c->mfma && gemm_mfma_fuses_qkv(n, d.hidden, b, n_qkv, c->skinny_ws != nullptr)) {
     // bias, RoPE, the compact q / k rows and the scatter of K and V into the cache are the projection's epilogue
-    QkvEpilogue qe{};
-    qe.row_pos = c->d_row_pos;
-    qe.row_lo = c->units_mode ? c->d_row_lo : nullptr;
-    qe.rope_cos = c->rope_cos;
-    qe.rope_sin = c->rope_sin;
-    qe.bias[0] = w.bq; qe.bias[1] = w.bk; qe.bias[2] = w.bv;
-    qe.q = c->q;
-    qe.k_compact = c->kc;
-    qe.k_cache = k_cache_l;
-    qe.v_cache = v_cache_l;
-    qe.q_dim = b.n_rows[0];
-    qe.kv_dim = b.n_rows[1];
+    const QkvEpilogue qe =
+        qkv_epilogue(c, w, b, c->d_row_pos, c->units_mode ? c->d_row_lo : nullptr, k_cache_l, v_cache_l);
     launch_gemm_mfma(reinterpret_cast<const bf16_t*>(c->hbuf), n, d.hidden, b, nullptr, n_qkv, EPI_QKV_ROPE, nullptr,
                      nullptr, s, c->skinny_ws, &qe);
     if (evs && !c->ev_light) {
@@ -568,9 +576,13 @@ keep_status layer_back(keep_ctx* c, int layer, int n, const void* o_rows, const 
     auto B = [](const void* p) { return reinterpret_cast<const bf16_t*>(p); };
     launch_gemm_mfma(B(o_rows), n, qd, bo, nullptr, d.hidden, EPI_RESIDUAL_STORE, B(x_in), c->x1, s, c->skinny_ws);
     EV(6);
-    launch_rmsnorm<bf16_t>(B(c->x1), B(w.ln2), n, d.hidden, d.rms_eps, reinterpret_cast<bf16_t*>(c->hbuf), s);
+    const bool fuse_norm = gemm_fuses_norm(n, d.hidden, bg, d.ffn_dim, EPI_SWIGLU_STORE, c->skinny_ws != nullptr);
+    const RowNorm norm{w.ln2, d.rms_eps};
+    if (!fuse_norm)
+      launch_rmsnorm<bf16_t>(B(c->x1), B(w.ln2), n, d.hidden, d.rms_eps, reinterpret_cast<bf16_t*>(c->hbuf), s);
     EV(7);
-    launch_gemm_mfma(B(c->hbuf), n, d.hidden, bg, w.wup, d.ffn_dim, EPI_SWIGLU_STORE, nullptr, c->act, s, c->skinny_ws);
+    launch_gemm_mfma(fuse_norm ? B(c->x1) : B(c->hbuf), n, d.hidden, bg, w.wup, d.ffn_dim, EPI_SWIGLU_STORE, nullptr,
+                     c->act, s, c->skinny_ws, nullptr, fuse_norm ? &norm : nullptr);
     EV(8);
     launch_gemm_mfma(B(c->act), n, d.ffn_dim, bd, nullptr, d.hidden, EPI_RESIDUAL_STORE, B(c->x1), x_out, s, c->skinny_ws);
   } else {
@@ -686,10 +698,13 @@ keep_status decode_impl(keep_ctx* c, const void* final_norm, const void* lm_head
   for (int t = 0; t < n_new; ++t) {
     // vocabulary projection of the newest hidden row, greedy choice
     float* lg = logits_out ? logits_out + (size_t)t * d.vocab : c->dec_logits;
-    launch_rmsnorm<T>(Typed<T>::p(x), Typed<T>::p(final_norm), 1, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
+    const bool head_norm = c->mfma && gemm_fuses_norm(1, d.hidden, bh, d.vocab, EPI_STORE_F32, c->skinny_ws != nullptr);
+    const RowNorm final_rn{final_norm, d.rms_eps};
+    if (!head_norm)
+      launch_rmsnorm<T>(Typed<T>::p(x), Typed<T>::p(final_norm), 1, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
     if (c->mfma)
-      launch_gemm_mfma(reinterpret_cast<const bf16_t*>(c->hbuf), 1, d.hidden, bh, nullptr, d.vocab, EPI_STORE_F32,
-                       nullptr, lg, s, c->skinny_ws);
+      launch_gemm_mfma(reinterpret_cast<const bf16_t*>(head_norm ? x : c->hbuf), 1, d.hidden, bh, nullptr, d.vocab,
+                       EPI_STORE_F32, nullptr, lg, s, c->skinny_ws, nullptr, head_norm ? &final_rn : nullptr);
     else
       launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, bh, nullptr, d.vocab, EPI_STORE_F32, nullptr, lg, s);
     launch_argmax(lg, d.vocab, c->d_dec + 2 * CAP + t, s);
@@ -714,7 +729,6 @@ keep_status decode_impl(keep_ctx* c, const void* final_norm, const void* lm_head
         if (sg.used) HIP_TRY(c, hipEventSynchronize(sg.done));
         att_plan.valid = false;
       }
-      launch_rmsnorm<T>(Typed<T>::p(x_cur), Typed<T>::p(w.ln1), 1, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
       GemmB b{};
       b.n_parts = 3;
       b.ptr[0] = w.wq; b.ptr[1] = w.wk; b.ptr[2] = w.wv;
@@ -727,14 +741,25 @@ keep_status decode_impl(keep_ctx* c, const void* final_norm, const void* lm_head
         set_w4(b, 2, c->w4[l].wv);
       }
       const int n_qkv = b.n_rows[0] + 2 * b.n_rows[1];
-      if (c->mfma)
-        launch_gemm_mfma(reinterpret_cast<const bf16_t*>(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32,
-                         nullptr, c->qkv_raw, s, c->skinny_ws);
-      else
-        launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32, nullptr, c->qkv_raw, s);
-      launch_rope_scatter<T>(c->qkv_raw, Typed<T>::p(w.bq), Typed<T>::p(w.bk), Typed<T>::p(w.bv), d_pos, 1, d.n_q_heads,
-                             d.n_kv_heads, d.head_dim, c->rope_cos, c->rope_sin, Typed<T>::p(c->q), Typed<T>::p(c->kc),
-                             Typed<T>::p(kl), Typed<T>::p(vl), s);
+      const bool fuse_qkv = c->mfma && gemm_mfma_fuses_qkv(1, d.hidden, b, n_qkv, c->skinny_ws != nullptr);
+      const bool fuse_norm = fuse_qkv && gemm_fuses_norm(1, d.hidden, b, n_qkv, EPI_QKV_ROPE, c->skinny_ws != nullptr);
+      if (!fuse_norm)
+        launch_rmsnorm<T>(Typed<T>::p(x_cur), Typed<T>::p(w.ln1), 1, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
+      if (fuse_qkv) {
+        const QkvEpilogue qe = qkv_epilogue(c, w, b, d_pos, nullptr, kl, vl);
+        const RowNorm norm{w.ln1, d.rms_eps};
+        launch_gemm_mfma(reinterpret_cast<const bf16_t*>(fuse_norm ? x_cur : c->hbuf), 1, d.hidden, b, nullptr, n_qkv,
+                         EPI_QKV_ROPE, nullptr, nullptr, s, c->skinny_ws, &qe, fuse_norm ? &norm : nullptr);
+      } else {
+        if (c->mfma)
+          launch_gemm_mfma(reinterpret_cast<const bf16_t*>(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32,
+                           nullptr, c->qkv_raw, s, c->skinny_ws);
+        else
+          launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32, nullptr, c->qkv_raw, s);
+        launch_rope_scatter<T>(c->qkv_raw, Typed<T>::p(w.bq), Typed<T>::p(w.bk), Typed<T>::p(w.bv), d_pos, 1,
+                               d.n_q_heads, d.n_kv_heads, d.head_dim, c->rope_cos, c->rope_sin, Typed<T>::p(c->q),
+                               Typed<T>::p(c->kc), Typed<T>::p(kl), Typed<T>::p(vl), s);
+      }
       if (c->mfma)
         launch_attn_mfma(reinterpret_cast<const bf16_t*>(c->q), reinterpret_cast<const bf16_t*>(kl),
                          reinterpret_cast<const bf16_t*>(vl), d_pos, plan.row_start.data(), sg.set_off, 0, pi.n_mem, 1,

@@ -628,16 +628,18 @@ static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
 
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws) {
   if (M <= 0 || N <= 0 || B.n_parts != 3) return false;
+  if (have_ws && gemm_skinny_fits(M, K, B, N, EPI_QKV_ROPE)) return true;
   if (have_ws && gemm_skinny_fits(M, K, B, N, EPI_STORE_F32)) return false;
   // every part a whole number of 128-column heads, so that a wave's columns never straddle q / k / v
   return big_tiles(M, K, B, N) && B.n_rows[0] % 128 == 0 && B.n_rows[1] % 128 == 0 && B.n_rows[2] % 128 == 0;
 }
 
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
-                      const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws, const QkvEpilogue* qkv) {
+                      const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws, const QkvEpilogue* qkv,
+                      const RowNorm* norm) {
   if (M <= 0 || N <= 0) return;
-  if (epilogue != EPI_QKV_ROPE && skinny_ws && gemm_skinny_fits(M, K, B, N, epilogue)) {
-    launch_gemm_skinny(A, M, K, B, B2, N, epilogue, residual, C, skinny_ws, s);
+  if (skinny_ws && gemm_skinny_fits(M, K, B, N, epilogue)) {
+    launch_gemm_skinny(A, M, K, B, B2, N, epilogue, residual, C, skinny_ws, s, qkv, norm);
     return;
   }
   MfmaB b;

@@ -100,6 +100,12 @@ struct QkvEpilogue {
   int32_t q_dim, kv_dim;
 };
 
+// RMSNorm weights (bf16) to apply to a single activation row in front of the product (gemm_fuses_norm).
+struct RowNorm {
+  const void* w;
+  float eps;
+};
+
 // One B operand made of up to three row blocks stacked along N (Wq | Wk | Wv).
 struct GemmB {
   const void* ptr[3];
@@ -181,17 +187,20 @@ void launch_score_finish(const float* rowmass, const int32_t* d_row_start, int32
 size_t gemm_ws_bytes();
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws = nullptr,
-                      const QkvEpilogue* qkv = nullptr);
-// true where launch_gemm_mfma would run this QKV projection on 256 x 256 tiles, the configuration that has the
-// fused epilogue (EPI_QKV_ROPE; a wave's 128 columns are one head); elsewhere the caller projects to fp32
-// (EPI_STORE_F32) and runs the RoPE/scatter kernel.
+                      const QkvEpilogue* qkv = nullptr, const RowNorm* norm = nullptr);
+// true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows, weight-streaming kernel)
+bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
+// true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows
+// (weight-streaming kernel) and launches on 256 x 256 tiles (a wave's 128 columns are one head); elsewhere the
+// caller projects to fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel.
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // bf16 expansion of an INT4 matrix: out[rows, K] = bf16((code - zero) * scale)
 void launch_dequant_int4(const void* codes, const void* scale_zero, int32_t rows, int32_t K, void* out, hipStream_t s);
 size_t gemm_skinny_ws_bytes();
 bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue);
 void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
-                        const bf16_t* residual, void* C, void* ws, hipStream_t s);
+                        const bf16_t* residual, void* C, void* ws, hipStream_t s, const QkvEpilogue* qkv,
+                        const RowNorm* norm);
 // h_row_start / h_set_off / m / instr_off: the host copy of the layer's row layout (as for
 // launch_build_rows), from which the work list is planned; h_stage: pinned host ints
 // (attn_mfma_stage_ints), d_scratch: device bytes (attn_mfma_scratch_bytes).

@@ -1,0 +1,54 @@
+"""Launches of up to 16 rows (the weight-streaming projections) at the edges of their tiles, against the oracle: a unit
+cached on its own and one decoded token, for row counts around the limit and for widths that leave waves without a
+step (K < 512), a step more on some waves than on others, and part-filled tiles of weight rows."""
+import numpy as np
+import pytest
+import torch
+
+import keep_synth as ks
+from oracle import keep_oracle as ko
+from gpu_util import Problem, max_rel, to_np
+from test_gpu_decode import head_weights
+
+pytestmark = pytest.mark.gpu
+
+# 7 query heads on 1 KV head, K = 448 (7 steps for 8 waves), FFN 1344 (21 steps); and K = 8256 (129 steps, a row of
+# activations beyond the two vectors a thread keeps in registers) with tiles of 9 units
+NARROW = ks.ModelShape(2, 448, 7, 1, 128, 1344, 1031, 1.0e6, 1e-6, "bf16")
+WIDE = ks.ModelShape(2, 8256, 2, 1, 128, 320, 211, 1.0e6, 1e-6, "bf16")
+
+
+@pytest.mark.parametrize("shape", [NARROW, WIDE], ids=["narrow", "wide"])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17])
+def test_few_rows_match_oracle(shape, n):
+    pb = Problem(shape, [n], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)
+    ctx = pb.context(max_tokens=n + 2)
+    assert ctx.uses_mfma
+    L = shape.n_layers
+    kc = torch.zeros((L, n + 1, shape.n_kv_heads, shape.head_dim), dtype=torch.bfloat16, device="cuda")
+    vc = torch.zeros_like(kc)
+    k1, v1 = kc[:, :n].contiguous(), vc[:, :n].contiguous()
+    ctx.precompute_group(pb.ids[:n], k1, v1)
+    torch.cuda.synchronize()
+    for l in range(L):      # (the oracle made the same unit's caches for the problem)
+        ek, ev = max_rel(to_np(k1[l]), pb.kb[l][0]), max_rel(to_np(v1[l]), pb.vb[l][0])
+        print(n, "layer", l, "K %.2e V %.2e" % (ek, ev))
+        assert ek < 2e-2 and ev < 2e-2
+
+    # one token decoded behind the unit, on the oracle's caches
+    for l in range(L):
+        kc[l, :n], vc[l, :n] = pb.kb_t[l][0].cuda(), pb.vb_t[l][0].cuda()
+    fn, lm = head_weights(shape)
+    x = torch.randn(shape.hidden, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
+    lg = torch.empty((2, shape.vocab), dtype=torch.float32, device="cuda")
+    toks = ctx.decode(fn.cuda(), lm.cuda(), x.cuda(), kc, vc, n, 2, logits_out=lg)
+    pad = lambda rows: [np.concatenate([r[0], np.zeros((1,) + r[0].shape[1:])]) for r in rows]
+    kr, vr = pad(pb.kb), pad(pb.vb)
+    _, ref = ko.greedy_decode(pb.sh, pb.layers, pb.embed, ks.to_numpy_f64(fn), ks.to_numpy_f64(lm), ks.to_numpy_f64(x),
+                              kr, vr, n, 2, forced_tokens=toks)
+    for t in range(2):
+        e = max_rel(to_np(lg)[t], ref[t])
+        print(n, "token", t, "logits %.2e" % e)
+        assert e < 2e-2
+    for l in range(L):
+        assert max_rel(to_np(kc[l, n]), kr[l][n]) < 2e-2 and max_rel(to_np(vc[l, n]), vr[l][n]) < 2e-2
