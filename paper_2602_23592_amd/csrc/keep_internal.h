@@ -237,13 +237,21 @@ void launch_score_mfma(const bf16_t* q, const bf16_t* k_compact, const float* ls
 // h_want: HOST [m + 1] flags or NULL: compute only the rows S[a, .] of the flagged source blocks (block m is
 // the instruction); the other rows of S are left untouched.
 
+// Candidates given as indices into a table of all memories, all in device memory: the selection forms the candidates'
+// lengths (cand_len) and their sum (cand_total) itself, settles budgets that keep all or none of the candidates
+// (hops_run 0) and writes the memories' indices instead of slots.
+struct SelectPrep {
+  const int32_t* groups;     // [m]
+  const int32_t* group_len;  // [n_groups]
+  int32_t n_groups;
+  int32_t* cand_len;         // [m]: also the launch's d_cand_len
+  int32_t* cand_total;
+};
+
 // multi-hop selection on the device; d_out: [0] = n_next, [1] = hops_run, [2..] = slots kept (ascending)
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
-                   int32_t mode, int32_t hops, float* d_work /*[(m+1)*m + 2m]*/, int32_t* d_iwork /*[4m]*/,
-                   int32_t* d_out /*[m+2]*/, hipStream_t s, bool set_only = false,
-                   const int32_t* d_cand_total = nullptr, const int32_t* d_id_map = nullptr);
-// d_cand_total (device scalar or NULL): sum of d_cand_len; when given, the kernel itself settles budgets that
-// keep all or none of the candidates (hops_run 0).  d_id_map (device [m] or NULL): ids written instead of slots.
+                   int32_t mode, int32_t hops, float* d_tot /*[m+1]*/, int32_t* d_out /*[m+2]*/, hipStream_t s,
+                   bool set_only = false, const SelectPrep* prep = nullptr);
 // set_only: the propagation averages the normalised rows of the relevant set alone (the query's row
 // only initialises the importance); default: the query stays a source at every hop.
 

@@ -1,74 +1,217 @@
 // Multi-hop importance propagation and selection (Section 4.2 of the paper:
 // initialisation, importance propagation, convergence check) on the device.
 //
-// One workgroup.  Every floating-point value that decides the selection is
-// computed in binary32 in a fixed order (sums over candidates in ascending
-// order, one division each), so the result is a pure function of S.
+// Every floating-point value that decides the selection is computed in binary32 in a fixed order (sums over
+// candidates in ascending order, one division each), so the result is a pure function of S.
+//
+// Two kernels: k_row_totals (many workgroups: reading S once needs more than one CU) and k_select (one workgroup:
+// what is left is a chain of small steps that depend on each other).
 #include "keep_internal.h"
 
 namespace keep {
 
 constexpr int SEL_THREADS = 1024;
 
-// rank every candidate by (importance descending, index ascending) and mark the
-// ones taken: the first k of the order (count mode) or a walk of the order that
-// takes a memory iff it still fits the token budget (token mode).  All arrays in LDS.
-// `imp` is consumed: in token mode its storage holds the lengths in rank order, then the walk's decisions.
-__device__ void take(float* imp, int m, const int32_t* len, int k_count, int token_budget, int mode,
-                     int32_t* order, int32_t* taken) {
-  int my_rank[6];  // ranks of this thread's candidates (m <= 6000, 1024 threads)
-  int n_mine = 0;
-  for (int b = threadIdx.x; b < m; b += SEL_THREADS) {
-    const float v = imp[b];
-    int rank = 0;
-    for (int c = 0; c < m; ++c) {
-      const float u = imp[c];
-      rank += (u > v) || (u == v && c < b);
-    }
-    my_rank[n_mine++] = rank;
-    order[rank] = b;
-    if (mode == KEEP_BUDGET_GROUP_COUNT) taken[b] = rank < k_count;
+// ---------------------------------------------------------------------------------------------
+// Row totals of S, each summed one element after the other in ascending order.
+//
+// A workgroup owns 16 rows.  Waves 1..4 fetch the next 256 columns into LDS (consecutive threads on consecutive
+// columns) while 16 lanes of wave 0 add the present ones, so the kernel costs the chain of m dependent additions and
+// no memory latency beyond the first block's: 8 us at 1024 candidates.  The last workgroup instead forms the candidates' lengths and their
+// total for callers that pass the memories' indices (`prep`).
+// ---------------------------------------------------------------------------------------------
+constexpr int RT_ROWS = 16, RT_COLS = 256, RT_LD = RT_COLS + 4;
+constexpr int RT_THREADS = 64 + RT_COLS;
+
+// Lengths of the candidates in candidate order and their total.  Indices are clamped into the length table so that a
+// bad id cannot make the kernel read out of bounds.
+__device__ void prepare_lengths(const SelectPrep& p, int m) {
+  __shared__ int s_part[RT_THREADS / 64];
+  int sum = 0;
+  for (int i = threadIdx.x; i < m; i += RT_THREADS) {
+    const int g = min(max(p.groups[i], 0), p.n_groups - 1);
+    const int len = p.group_len[g];
+    p.cand_len[i] = len;
+    sum += len;
   }
-  __syncthreads();  // every importance has been read, every rank is known
-  if (mode != KEEP_BUDGET_GROUP_COUNT) {
-    // The walk itself is sequential (a memory that does not fit is skipped, the next one may fit), so it is
-    // given the lengths in rank order and writes its decisions back in place: one LDS read and one write per
-    // step with independent addresses; the scatter to `taken` is parallel again.
-    int32_t* olen = reinterpret_cast<int32_t*>(imp);
-    n_mine = 0;
-    for (int b = threadIdx.x; b < m; b += SEL_THREADS) olen[my_rank[n_mine++]] = len[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int t = 0;
+    for (int w = 0; w < RT_THREADS / 64; ++w) t += s_part[w];
+    *p.cand_total = t;  // written, not accumulated: nothing of an earlier call survives
+  }
+}
+
+__global__ void __launch_bounds__(RT_THREADS)
+    k_row_totals(const float* __restrict__ S, int m, float* __restrict__ tot, SelectPrep prep) {
+  if (prep.groups && blockIdx.x + 1 == gridDim.x) {
+    prepare_lengths(prep, m);
+    return;
+  }
+  __shared__ __attribute__((aligned(16))) float tile[2][RT_ROWS][RT_LD];
+  const int tid = threadIdx.x;
+  const int a0 = blockIdx.x * RT_ROWS;
+  const int rows = min(RT_ROWS, m + 1 - a0);
+  const int n_blocks = (m + RT_COLS - 1) / RT_COLS;
+  const int c = tid - 64;  // loaders: the column
+  float total = 0.f;
+  for (int k = -1; k < n_blocks; ++k) {
+    if (tid >= 64) {
+      const int col = (k + 1) * RT_COLS + c;
+      if (k + 1 < n_blocks && col < m) {
+        const float* src = S + (size_t)a0 * m + col;
+        float v[RT_ROWS];
+#pragma unroll
+        for (int r = 0; r < RT_ROWS; ++r) v[r] = r < rows ? src[(size_t)r * m] : 0.f;
+#pragma unroll
+        for (int r = 0; r < RT_ROWS; ++r) tile[(k + 1) & 1][r][c] = v[r];
+      }
+    } else if (k >= 0 && tid < rows) {
+      const float* t = tile[k & 1][tid];
+      const int cols = min(RT_COLS, m - k * RT_COLS);
+      int j = 0;
+      for (; j + 32 <= cols; j += 32) {
+        float4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const float4*>(t + j + 4 * q);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          total = total + v[q].x;
+          total = total + v[q].y;
+          total = total + v[q].z;
+          total = total + v[q].w;
+        }
+      }
+      for (; j < cols; ++j) total = total + t[j];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      int used = 0;
-      for (int i = 0; i < m; ++i) {
-        const int l = olen[i];
-        const int fits = used + l <= token_budget;
-        olen[i] = fits;
-        used += fits ? l : 0;
+  }
+  if (tid < rows) tot[a0 + tid] = total;
+}
+
+// ---------------------------------------------------------------------------------------------
+// k_select
+// ---------------------------------------------------------------------------------------------
+// Sort key: ascending keys are (importance descending, index ascending).  -0 counts as +0; a NaN, which no score of
+// attention mass is, comes behind every number.
+__device__ __forceinline__ uint64_t sel_key(float v, int b) {
+  uint32_t hi = 0xFFFFFFFFu;
+  if (v == v) {
+    const uint32_t u = v == 0.f ? 0u : __float_as_uint(v);
+    hi = ~(u & 0x80000000u ? ~u : u | 0x80000000u);  // at most 0xFF800000 (-inf)
+  }
+  return (uint64_t)hi << 32 | (uint32_t)b;
+}
+
+// Bitonic sort of P keys (a power of two) in LDS, ascending.  A wave's pairs lie in 128 consecutive keys as long as
+// partners are at most 64 apart, so only the wider steps need the workgroup's barrier.
+__device__ void sel_sort(uint64_t* key, int P) {
+  bool wide = true;  // the step before crossed waves (the caller's writes did)
+  for (int k = 2; k <= P; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      if (wide || j > 64)
+        __syncthreads();
+      else
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      wide = j > 64;
+      for (int p = threadIdx.x; p < (P >> 1); p += SEL_THREADS) {
+        const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1));
+        const uint64_t x = key[i], y = key[i + j];
+        if ((x > y) == ((i & k) == 0)) {
+          key[i] = y;
+          key[i + j] = x;
+        }
       }
     }
+  __syncthreads();
+}
+
+// Mark what is taken of the order: its first k (count mode) or a walk of it that takes a memory iff it still fits the
+// token budget (token mode).  key[b], b < m: the candidates' keys.
+//
+// Ranking by sorting: 1024 candidates against each other are 2^20 comparisons for one CU, the sort is 55 short steps.
+// The walk goes in chunks of 64 through one wave: of those that fit what is left, all up to the first whose running
+// sum does not are taken at once, that one is passed over, and so on; what does not fit once never will.
+__device__ void take(uint64_t* key, int m, int P, const int32_t* len, int k_count, int token_budget, int mode,
+                     uint8_t* taken) {
+  for (int b = m + threadIdx.x; b < P; b += SEL_THREADS) key[b] = ~0ull;
+  sel_sort(key, P);
+  if (mode == KEEP_BUDGET_GROUP_COUNT) {
+    for (int i = threadIdx.x; i < m; i += SEL_THREADS) {
+      const uint64_t e = key[i];
+      // (nothing is greater than a NaN: its rank is 0)
+      taken[(uint32_t)e] = (uint32_t)(e >> 32) == 0xFFFFFFFFu ? k_count > 0 : i < k_count;
+    }
+  } else if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    int left = token_budget;
+    for (int c0 = 0; c0 < m; c0 += 64) {
+      const bool valid = c0 + lane < m;
+      const int b = valid ? (int)(uint32_t)key[c0 + lane] : 0;
+      const int l = valid ? len[b] : 0;
+      uint64_t cand = __ballot(valid && l <= left), got = 0;
+      while (cand) {
+        int64_t sum = cand >> lane & 1 ? l : 0;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int64_t t = __shfl_up((long long)sum, o, 64);
+          if (lane >= o) sum += t;
+        }
+        const uint64_t over = __ballot((cand >> lane & 1) && sum > left);
+        const int f = over ? __builtin_ctzll(over) : 64;  // the first that does not fit behind those before it
+        got |= f < 64 ? cand & ((1ull << f) - 1) : cand;
+        if (f > 0) left -= (int)__shfl((long long)sum, f - 1, 64);
+        cand = f < 63 ? cand & ~((2ull << f) - 1) : 0;
+        cand &= __ballot(l <= left);
+      }
+      if (valid) taken[b] = got >> lane & 1;
+    }
+  }
+  __syncthreads();
+}
+
+// The marked candidates in ascending order; returns how many.
+__device__ int compact(const uint8_t* taken, int m, int32_t* list, int* s_cnt /*[SEL_THREADS / 64]*/) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int n = 0;
+  for (int b0 = 0; b0 < m; b0 += SEL_THREADS) {
+    const int b = b0 + threadIdx.x;
+    const bool mine = b < m && taken[b];
+    const uint64_t votes = __ballot(mine);
+    if (lane == 0) s_cnt[wave] = __popcll(votes);
     __syncthreads();
-    for (int i = threadIdx.x; i < m; i += SEL_THREADS) taken[order[i]] = olen[i];
+    int at = n;
+    for (int w = 0; w < SEL_THREADS / 64; ++w) {
+      at += w < wave ? s_cnt[w] : 0;
+      n += s_cnt[w];
+    }
+    if (mine) list[at + __popcll(votes & ((1ull << lane) - 1))] = b;
     __syncthreads();
   }
+  return n;
 }
 
 // The normalised score of (a, b) is S[a, b] / total_a with total_a the sum of row a in ascending order
 // (0 where the row is empty); it is formed where it is used, only the row totals are kept.
+//
+// Bound by its chain of small steps.  It reads only the rows of S that the propagation averages, 16 loads in flight per
+// thread.  1024 candidates, 307 kept, three selections: 118 us; one workgroup that also summed the rows, ranked every
+// candidate against every other and walked budget and output list one by one took 1020 us.
 __global__ void __launch_bounds__(SEL_THREADS)
-    k_select(const float* __restrict__ S, int m, const int32_t* __restrict__ cand_len, int k_count, int token_budget,
-             int mode, int hops, int set_only, int tile_rows, float* __restrict__ work, int32_t* __restrict__ iwork,
+    k_select(const float* __restrict__ S, int m, int P, const int32_t* __restrict__ cand_len, int k_count,
+             int token_budget, int mode, int hops, int set_only, const float* __restrict__ row_tot,
              int32_t* __restrict__ out, const int32_t* __restrict__ cand_total, const int32_t* __restrict__ id_map) {
-  extern __shared__ float sel_smem[];
-  float* tot = sel_smem;                                   // [m + 1] row totals
-  float* imp = tot + (m + 1);                              // [m]
-  int32_t* order = reinterpret_cast<int32_t*>(imp + m);    // [m]
-  int32_t* rel = order + m;                                // [m]
-  int32_t* rel2 = rel + m;                                 // [m]
-  int32_t* len = rel2 + m;                                 // [m]
-  __shared__ int s_same, s_cnt;
-  (void)work;
-  (void)iwork;
+  extern __shared__ __attribute__((aligned(16))) char sel_smem[];
+  uint64_t* key = reinterpret_cast<uint64_t*>(sel_smem);  // [P]
+  float* list_tot = reinterpret_cast<float*>(key + P);    // [m] row totals of the listed candidates
+  int32_t* list = reinterpret_cast<int32_t*>(list_tot + m);  // [m] the relevant set, ascending
+  int32_t* len = list + m;                                // [m]
+  uint8_t* rel = reinterpret_cast<uint8_t*>(len + m);     // [m]
+  uint8_t* rel2 = rel + m;                                // [m]
+  __shared__ int s_diff, s_cnt[SEL_THREADS / 64];
   // Callers that could not classify the budget on the host pass the candidates' token total: a budget that
   // takes every candidate or none is settled here without a selection (0 selections run), as the host does
   // for the other callers.
@@ -86,105 +229,74 @@ __global__ void __launch_bounds__(SEL_THREADS)
     }
   }
 
-  if (tile_rows > 0) {
-    // Row totals, each still summed one element after the other in ascending order, but read through LDS:
-    // blocks of tile_rows rows x 32 columns are fetched with consecutive threads on consecutive columns
-    // (a thread walking its own row of S directly touches a new cache line at every step).
-    float* tile = reinterpret_cast<float*>(len + m);  // [tile_rows][33]
-    for (int a0 = 0; a0 <= m; a0 += tile_rows) {
-      const int rows = min(tile_rows, m + 1 - a0);
-      float total = 0.f;
-      for (int b0 = 0; b0 < m; b0 += 32) {
-        const int cols = min(32, m - b0);
-        for (int i = threadIdx.x; i < rows * 32; i += SEL_THREADS) {
-          const int r = i >> 5, j = i & 31;
-          if (j < cols) tile[r * 33 + j] = S[(size_t)(a0 + r) * m + b0 + j];
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < rows)
-          for (int j = 0; j < cols; ++j) total = total + tile[threadIdx.x * 33 + j];
-        __syncthreads();
-      }
-      if ((int)threadIdx.x < rows) tot[a0 + threadIdx.x] = total;
-    }
-  } else {
-    for (int a = threadIdx.x; a <= m; a += SEL_THREADS) {
-      const float* row = S + (size_t)a * m;
-      float total = 0.f;
-      for (int b = 0; b < m; ++b) total = total + row[b];
-      tot[a] = total;
-    }
-  }
   for (int b = threadIdx.x; b < m; b += SEL_THREADS) len[b] = cand_len[b];
-  __syncthreads();
-  const float tq = tot[m];
-  for (int b = threadIdx.x; b < m; b += SEL_THREADS) imp[b] = tq > 0.f ? S[(size_t)m * m + b] / tq : 0.f;
-  __syncthreads();
-  take(imp, m, len, k_count, token_budget, mode, order, rel);
+  const float tq = row_tot[m];
+  for (int b = threadIdx.x; b < m; b += SEL_THREADS) key[b] = sel_key(tq > 0.f ? S[(size_t)m * m + b] / tq : 0.f, b);
+  take(key, m, P, len, k_count, token_budget, mode, rel);
+  int n_rel = compact(rel, m, list, s_cnt);
   int runs = 1;
   const int max_runs = hops > 1 ? hops : 1;
   while (runs < max_runs) {
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    {
-      int c = 0;  // (integer count: the order of the additions does not matter)
-      for (int a = threadIdx.x; a < m; a += SEL_THREADS) c += rel[a];
-      if (c) atomicAdd(&s_cnt, c);
-    }
+    for (int i = threadIdx.x; i < n_rel; i += SEL_THREADS) list_tot[i] = row_tot[list[i]];
     __syncthreads();
     // sources of the propagation: the query and the relevant set, or (set_only: the section's wording taken
     // literally) the relevant set alone; an empty source set leaves the importance at zero
-    const int n_src = (set_only ? 0 : 1) + s_cnt;
+    const int n_src = (set_only ? 0 : 1) + n_rel;
     const float denom = (float)n_src;
     for (int b = threadIdx.x; b < m; b += SEL_THREADS) {
       float acc = (!set_only && tq > 0.f) ? S[(size_t)m * m + b] / tq : 0.f;
-      for (int a = 0; a < m; ++a)
-        if (rel[a]) {
-          const float ta = tot[a];
-          acc = acc + (ta > 0.f ? S[(size_t)a * m + b] / ta : 0.f);
+      constexpr int U = 16;
+      int i = 0;
+      for (; i + U <= n_rel; i += U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = S[(size_t)list[i + u] * m + b];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float ta = list_tot[i + u];
+          acc = acc + (ta > 0.f ? v[u] / ta : 0.f);
         }
-      imp[b] = n_src > 0 ? acc / denom : acc;
+      }
+      for (; i < n_rel; ++i) {
+        const float ta = list_tot[i];
+        acc = acc + (ta > 0.f ? S[(size_t)list[i] * m + b] / ta : 0.f);
+      }
+      key[b] = sel_key(n_src > 0 ? acc / denom : acc, b);
     }
-    __syncthreads();
-    take(imp, m, len, k_count, token_budget, mode, order, rel2);
+    if (threadIdx.x == 0) s_diff = 0;
+    take(key, m, P, len, k_count, token_budget, mode, rel2);
     ++runs;
-    if (threadIdx.x == 0) s_same = 1;
-    __syncthreads();
-    {
-      int differs = 0;
-      for (int a = threadIdx.x; a < m; a += SEL_THREADS) differs |= (rel[a] != rel2[a]);
-      if (differs) s_same = 0;  // (every writer writes the same value)
+    int differs = 0;
+    for (int a = threadIdx.x; a < m; a += SEL_THREADS) {
+      differs |= rel[a] != rel2[a];
+      rel[a] = rel2[a];
     }
+    if (differs) s_diff = 1;  // (every writer writes the same value)
     __syncthreads();
-    const int same = s_same;
-    __syncthreads();
-    if (same) break;
-    for (int b = threadIdx.x; b < m; b += SEL_THREADS) rel[b] = rel2[b];
-    __syncthreads();
+    const int changed = s_diff;
+    if (!changed) break;
+    n_rel = compact(rel, m, list, s_cnt);  // (its barriers order this read of s_diff before the next clearing)
   }
+  for (int i = threadIdx.x; i < n_rel; i += SEL_THREADS) out[2 + i] = id_map ? id_map[list[i]] : list[i];
   if (threadIdx.x == 0) {
-    int n = 0;
-    for (int a = 0; a < m; ++a)
-      if (rel[a]) out[2 + n++] = id_map ? id_map[a] : a;
-    out[0] = n;
+    out[0] = n_rel;
     out[1] = runs;
   }
 }
 
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
-                   int32_t mode, int32_t hops, float* d_work, int32_t* d_iwork, int32_t* d_out, hipStream_t s,
-                   bool set_only, const int32_t* d_cand_total, const int32_t* d_id_map) {
-  size_t sh = ((size_t)(m + 1) + m) * sizeof(float) + (size_t)4 * m * sizeof(int32_t);  // <= 160 KB: m <= 6000
-  // room for the staging tile of the row totals (256 rows x 33 floats) unless the arrays leave none
-  int tile_rows = 0;
-  if (sh + (size_t)256 * 33 * sizeof(float) <= (size_t)160 * 1024 - 256) {
-    tile_rows = 256;
-    sh += (size_t)256 * 33 * sizeof(float);
-  }
+                   int32_t mode, int32_t hops, float* d_tot, int32_t* d_out, hipStream_t s, bool set_only,
+                   const SelectPrep* prep) {
+  int P = 2;
+  while (P < m) P <<= 1;
+  const size_t sh = (size_t)P * 8 + (size_t)m * (3 * 4 + 2);  // <= 147 KB: m <= 6000
   static std::atomic<uint64_t> attr_done{0};
   set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select), 160 * 1024 - 256);
-  hipLaunchKernelGGL(k_select, dim3(1), dim3(SEL_THREADS), sh, s, S, m, d_cand_len, k_count, token_budget, mode, hops,
-                     set_only ? 1 : 0, tile_rows, d_work, d_iwork, d_out, d_cand_total, d_id_map);
+  const SelectPrep pr = prep ? *prep : SelectPrep{};
+  const int blocks = (m + 1 + RT_ROWS - 1) / RT_ROWS + (prep ? 1 : 0);
+  hipLaunchKernelGGL(k_row_totals, dim3(blocks), dim3(RT_THREADS), 0, s, S, m, d_tot, pr);
+  hipLaunchKernelGGL(k_select, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode, hops,
+                     set_only ? 1 : 0, d_tot, d_out, pr.cand_total, pr.groups);
 }
 
 }  // namespace keep

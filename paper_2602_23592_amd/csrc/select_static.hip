@@ -1,6 +1,6 @@
 // keep_select_groups_static: the multi-hop selection for callers that cannot allocate.
 //
-// Same kernel as keep_select_groups (k_select).  That entry point keeps the candidates' lengths and the
+// Same kernels as keep_select_groups (k_row_totals, k_select).  That entry point keeps the candidates' lengths and the
 // candidates' token total in the context's workspace (device memory the library allocated at keep_init);
 // here they live in a file-scope device array, so the call needs no context, no workspace and makes no
 // allocation of any kind.  Every GPU the library runs on holds its own copy of the array until the process
@@ -20,37 +20,15 @@ using namespace keep;
 
 namespace {
 
-// scratch: [0, KEEP_STATIC_MAX_CANDIDATES) lengths of the candidates, then one word: their sum
-constexpr int SCRATCH_WORDS = KEEP_STATIC_MAX_CANDIDATES + 64;
+// scratch: [0, KEEP_STATIC_MAX_CANDIDATES) lengths of the candidates, one word: their sum, and from SCRATCH_TOTALS on
+// the row totals of S (floats)
+constexpr int SCRATCH_TOTALS = KEEP_STATIC_MAX_CANDIDATES + 64;
+constexpr int SCRATCH_WORDS = SCRATCH_TOTALS + KEEP_STATIC_MAX_CANDIDATES + 64;
 static __device__ __align__(256) int32_t scratch[SCRATCH_WORDS];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_mu;
 int32_t* g_scratch_ptr[MAX_DEVICES] = {};  // device address of `scratch` on each GPU (its own copy at its own address)
-
-// Lengths of the candidates in candidate order and their total.  One workgroup; indices are clamped into
-// the length table so that a bad id cannot make the kernel read out of bounds.
-__global__ void __launch_bounds__(1024)
-    k_static_prepare(const int32_t* __restrict__ groups, int m, const int32_t* __restrict__ group_len, int n_groups,
-                     int32_t* __restrict__ cand_len, int32_t* __restrict__ cand_total) {
-  __shared__ int s_part[16];
-  int sum = 0;
-  for (int i = threadIdx.x; i < m; i += 1024) {
-    const int g = min(max(groups[i], 0), n_groups - 1);
-    const int len = group_len[g];
-    cand_len[i] = len;
-    sum += len;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-  if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int w = 0; w < 16; ++w) t += s_part[w];
-    *cand_total = t;  // written, not accumulated: nothing of an earlier call survives
-  }
-}
 
 keep_status fail_static(keep_status st, const char* text) {
   set_init_error(text);
@@ -98,13 +76,13 @@ extern "C" keep_status keep_select_groups_static(const float* S, const int32_t* 
   hipStream_t s = static_cast<hipStream_t>(stream);
   int32_t* cand_len = sp;
   int32_t* cand_total = sp + KEEP_STATIC_MAX_CANDIDATES;
-  hipLaunchKernelGGL(k_static_prepare, dim3(1), dim3(1024), 0, s, groups, n_sel, group_len, n_groups_total, cand_len,
-                     cand_total);
   // the two budgets, as keep_select_groups forms them on the host
   const int k_count = std::max(0, std::min<int>(n_sel, (int)ceil((double)ratio_next * (double)n_groups_total - 1.0e-3)));
   const int token_budget = (int)floor((double)ratio_next * (double)mem_tokens + 1.0e-3);
-  launch_select(S, n_sel, cand_len, k_count, token_budget, budget_mode, hops, nullptr, nullptr, result, s,
-                propagation_sources == KEEP_SOURCES_SET_ONLY, cand_total, groups);
+  const SelectPrep prep{groups, group_len, n_groups_total, cand_len, cand_total};
+  launch_select(S, n_sel, cand_len, k_count, token_budget, budget_mode, hops,
+                reinterpret_cast<float*>(sp + SCRATCH_TOTALS), result, s,
+                propagation_sources == KEEP_SOURCES_SET_ONLY, &prep);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_static(KEEP_ERR_HIP, hipGetErrorString(e));
   return KEEP_OK;
