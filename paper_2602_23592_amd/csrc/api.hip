@@ -91,6 +91,7 @@ struct keep_ctx {
   int32_t* h_dec = nullptr;         // pinned [4 * KEEP_DECODE_MAX_TOKENS]: positions, fed tokens, results
   int32_t* d_dec = nullptr;         // device mirror
   float* dec_logits = nullptr;      // [vocab]
+  uint64_t* argmax_part = nullptr;  // [ARGMAX_BLOCKS]
   float* h_S = nullptr;             // [(max_groups+1) * max_groups]
   int32_t* h_token_ids = nullptr;   // [max_tokens]
 
@@ -253,6 +254,7 @@ uint64_t workspace_bytes(const keep_model_desc* d) {
   t += align256((z.G + 1) * sizeof(float));                            // sel_tot
   t += align256((z.G + 2) * sizeof(int32_t));                          // sel_out
   t += align256(4 * KEEP_DECODE_MAX_TOKENS * 4) + align256((size_t)d->vocab * sizeof(float));  // decode
+  t += align256(ARGMAX_BLOCKS * sizeof(uint64_t));
   t += 2 * align256(z.M * sizeof(int32_t));                            // row_lo, row_list
   t += 3 * align256(z.M * sizeof(int32_t));                            // token deviation, flags, kept list
   return t;
@@ -706,7 +708,7 @@ keep_status decode_impl(keep_ctx* c, const void* final_norm, const void* lm_head
                        EPI_STORE_F32, nullptr, lg, s, c->skinny_ws, nullptr, head_norm ? &final_rn : nullptr);
     else
       launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, bh, nullptr, d.vocab, EPI_STORE_F32, nullptr, lg, s);
-    launch_argmax(lg, d.vocab, c->d_dec + 2 * CAP + t, s);
+    launch_argmax(lg, d.vocab, c->d_dec + 2 * CAP + t, c->argmax_part, s);
     HIP_TRY(c, hipGetLastError());
     if (t + 1 == n_new) break;
     // the chosen (or forced) token at position n_ctx + t through every layer
@@ -972,6 +974,7 @@ keep_status keep_init(const keep_model_desc* desc, const keep_layer_weights* lay
   TRY_INIT(pin_alloc(c, &c->h_dev, z.M * 4));
   TRY_INIT(dev_alloc(c, &c->d_dec, 4 * KEEP_DECODE_MAX_TOKENS * 4));
   TRY_INIT(dev_alloc(c, &c->dec_logits, (size_t)desc->vocab * sizeof(float)));
+  TRY_INIT(dev_alloc(c, &c->argmax_part, ARGMAX_BLOCKS * sizeof(uint64_t)));
   TRY_INIT(pin_alloc(c, &c->h_S, (z.G + 1) * z.G * sizeof(float)));
   TRY_INIT(pin_alloc(c, &c->h_token_ids, z.M * 4));
   auto mk_events = [&]() -> keep_status {

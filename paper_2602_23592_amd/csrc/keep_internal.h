@@ -160,8 +160,9 @@ void launch_rows_gather_list(const T* x_src, const int32_t* d_idx, int32_t n_row
 void launch_select_tokens(const float* d_deviation, int32_t n, int32_t k, int32_t n_tail, int32_t* d_flags,
                           int32_t* d_list, hipStream_t s);
 
-// out[0] = index of the largest of logits[0..n), the lowest index among equal values
-void launch_argmax(const float* logits, int32_t n, int32_t* out, hipStream_t s);
+// out[0] = index of the largest of logits[0..n), the lowest index among equal values; n >= 1
+constexpr int ARGMAX_BLOCKS = 128;
+void launch_argmax(const float* logits, int32_t n, int32_t* out, uint64_t* d_part /*[ARGMAX_BLOCKS]*/, hipStream_t s);
 
 // generic (scalar FMA) kernels
 template <typename T>

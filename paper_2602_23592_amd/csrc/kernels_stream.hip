@@ -397,42 +397,62 @@ void launch_rows_gather_list(const T* x_src, const int32_t* d_idx, int32_t n_row
   hipLaunchKernelGGL(k_rows_gather_list<T>, dim3(n_rows_dst), dim3(256), 0, s, x_src, d_idx, width, x_dst);
 }
 
-// Greedy choice over one row of logits: the largest value, the lowest index among equal ones.
-// One workgroup; every thread scans a strided slice (ascending, so it keeps the first of equal
-// values), then a fixed tree over (value, index) pairs.
-__global__ void __launch_bounds__(1024) k_argmax(const float* __restrict__ logits, int n, int32_t* __restrict__ out) {
-  __shared__ float s_v[1024];
-  __shared__ int s_i[1024];
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    const float v = logits[i];
-    if (v > best || bi == 0x7fffffff) {
-      best = v;
-      bi = i;
-    }
+// Greedy choice over one row of logits: the largest value, the lowest index among equal ones; a NaN is chosen only
+// where there is nothing else.
+//
+// Bound by latency, not by its 0.6 MB (152064 logits): one workgroup reading them alone took 69 us, so
+// ARGMAX_BLOCKS workgroups reduce a strided share each and a second launch their keys (10 us for both; a ticket that
+// lets the last workgroup finish would need a device-wide release in every one).  Values and indices travel as one
+// key, larger is better, so the result does not depend on the order of the reduction.
+__device__ __forceinline__ uint64_t argmax_key(float v, int i) {
+  uint32_t o = 0;
+  if (v == v) {
+    const uint32_t u = v == 0.f ? 0u : __float_as_uint(v);  // (-0 equals +0)
+    o = u & 0x80000000u ? ~u : u | 0x80000000u;             // at least 0x007FFFFF (-inf)
   }
-  s_v[threadIdx.x] = best;
-  s_i[threadIdx.x] = bi;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      const float v2 = s_v[threadIdx.x + w];
-      const int i2 = s_i[threadIdx.x + w];
-      const float v1 = s_v[threadIdx.x];
-      const int i1 = s_i[threadIdx.x];
-      if (i2 != 0x7fffffff && (i1 == 0x7fffffff || v2 > v1 || (v2 == v1 && i2 < i1))) {
-        s_v[threadIdx.x] = v2;
-        s_i[threadIdx.x] = i2;
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = s_i[0];
+  return (uint64_t)o << 32 | ~(uint32_t)i;
 }
 
-void launch_argmax(const float* logits, int32_t n, int32_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_argmax, dim3(1), dim3(1024), 0, s, logits, n, out);
+template <int T>
+__device__ __forceinline__ uint64_t argmax_reduce(uint64_t best) {
+  __shared__ uint64_t s_best[T / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint64_t other = __shfl_xor((unsigned long long)best, o, 64);
+    best = other > best ? other : best;
+  }
+  if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) best = s_best[w] > best ? s_best[w] : best;
+  return best;
+}
+
+__global__ void __launch_bounds__(256) k_argmax_part(const float* __restrict__ logits, int n, uint64_t* __restrict__ part) {
+  uint64_t best = 0;
+  constexpr int U = 8, STEP = ARGMAX_BLOCKS * 256;
+  for (long i0 = (long)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += (long)U * STEP) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + (long)u * STEP < n ? logits[i0 + (long)u * STEP] : 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t k = argmax_key(v[u], (int)(i0 + (long)u * STEP));
+      best = i0 + (long)u * STEP < n && k > best ? k : best;
+    }
+  }
+  best = argmax_reduce<256>(best);
+  if (threadIdx.x == 0) part[blockIdx.x] = best;
+}
+
+__global__ void __launch_bounds__(ARGMAX_BLOCKS) k_argmax_final(const uint64_t* __restrict__ part, int32_t* __restrict__ out) {
+  const uint64_t best = argmax_reduce<ARGMAX_BLOCKS>(part[threadIdx.x]);
+  if (threadIdx.x == 0) *out = (int32_t)~(uint32_t)best;
+}
+
+void launch_argmax(const float* logits, int32_t n, int32_t* out, uint64_t* d_part, hipStream_t s) {
+  hipLaunchKernelGGL(k_argmax_part, dim3(ARGMAX_BLOCKS), dim3(256), 0, s, logits, n, d_part);
+  hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(ARGMAX_BLOCKS), 0, s, d_part, out);
 }
 
 // explicit instantiations
