@@ -63,7 +63,7 @@ struct keep_ctx {
   std::vector<void*> allocs;
   size_t bytes = 0;
   float *rope_cos = nullptr, *rope_sin = nullptr;
-  int32_t *d_token_ids = nullptr, *d_row_pos = nullptr, *d_row_slot = nullptr;
+  int32_t *d_token_ids = nullptr, *d_row_pos = nullptr;
   int32_t *d_set_off = nullptr, *d_row_start = nullptr, *d_gather_src = nullptr, *d_cand_len = nullptr;
   RealignSeg* d_segs = nullptr;
   void *xa = nullptr, *xb = nullptr, *hbuf = nullptr, *q = nullptr, *kc = nullptr, *o = nullptr, *x1 = nullptr,
@@ -238,7 +238,7 @@ uint64_t workspace_bytes(const keep_model_desc* d) {
   size_t half = (size_t)d->head_dim / 2;
   size_t t = 0;
   t += 2 * align256(z.M * half * sizeof(float));                       // rope cos, sin
-  t += 3 * align256(z.M * sizeof(int32_t));                            // token ids, row_pos, row_slot
+  t += 2 * align256(z.M * sizeof(int32_t));                            // token ids, row_pos
   t += 4 * align256((z.G + 2) * sizeof(int32_t));                      // set_off, row_start, gather_src, cand_len
   t += align256(z.G * sizeof(RealignSeg));
   t += 4 * align256(z.M * z.d * z.esz);                                // xa, xb, h, x1
@@ -356,9 +356,9 @@ struct LayerPlan {
 };
 
 // Fill the layer's staging slot (set offsets, compact row starts, re-align segments) and
-// enqueue its upload on the compute stream.
+// enqueue its upload on the compute stream (uploaded: the device holds the same tables already).
 keep_status stage_layer(keep_ctx* c, const keep_prompt* p, const PromptInfo& pi, int layer, const int32_t* groups,
-                        int m, const void* k_cache_l, const void* v_cache_l, bool blocks_at_dst, LayerPlan* plan) {
+                        int m, const void* k_cache_l, const void* v_cache_l, bool blocks_at_dst, LayerPlan* plan, bool uploaded = false) {
   Staging& st = c->stage[layer];
   if (st.used) HIP_TRY(c, hipEventSynchronize(st.done));
   plan->m = m;
@@ -402,6 +402,7 @@ keep_status stage_layer(keep_ctx* c, const keep_prompt* p, const PromptInfo& pi,
   plan->n_segs = ns;
   plan->n_realign_rows = rows;
   hipStream_t s = c->s_comp;
+  if (uploaded) return KEEP_OK;
   // one upload: the three int arrays and the segments that are in use
   const size_t G_cap = (size_t)std::max(1, c->d.max_groups);
   HIP_TRY(c, hipMemcpyAsync(c->d_set_off, st.set_off, table_seg_offset_ints(G_cap) * 4 + (size_t)ns * sizeof(RealignSeg),
@@ -439,13 +440,15 @@ keep_status layer_front(keep_ctx* c, const PromptInfo& pi, int layer, const Laye
   launch_realign<T>(c->d_segs, plan.n_segs, plan.n_realign_rows, d.n_kv_heads, d.head_dim, c->rope_cos, c->rope_sin,
                     Typed<T>::p(k_cache_l), Typed<T>::p(v_cache_l), s);
   if (evs && !c->ev_light) HIP_TRY(c, hipEventRecord(evs[1], s));
-  launch_build_rows(c->d_set_off, c->d_row_start, plan.m, pi.n_mem, n, c->d_row_pos, c->d_row_slot, s);
+  const RowMap map{c->d_set_off, c->d_row_start, plan.m, pi.n_mem, c->d_row_pos};
   const T* x = Typed<T>::p(x_in);
-  if (!x) {
+  const bool from_embed = !x;  // (the gather reads the positions: they come first)
+  if (from_embed) {
+    launch_build_rows(map, n, s);
     launch_embed_gather<T>(Typed<T>::p(c->embed), c->d_token_ids, c->d_row_pos, n, d.hidden, Typed<T>::p(c->xa), s);
     x = Typed<T>::p(c->xa);
   }
-  launch_rmsnorm<T>(x, Typed<T>::p(w.ln1), n, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
+  launch_rmsnorm<T>(x, Typed<T>::p(w.ln1), n, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s, from_embed ? nullptr : &map);
   if (evs && !c->ev_light) HIP_TRY(c, hipEventRecord(evs[2], s));
   GemmB b{};
   b.n_parts = 3;
@@ -889,7 +892,6 @@ keep_status keep_init(const keep_model_desc* desc, const keep_layer_weights* lay
   TRY_INIT(dev_alloc(c, &c->rope_sin, z.M * half * sizeof(float)));
   TRY_INIT(dev_alloc(c, &c->d_token_ids, z.M * 4));
   TRY_INIT(dev_alloc(c, &c->d_row_pos, z.M * 4));
-  TRY_INIT(dev_alloc(c, &c->d_row_slot, z.M * 4));
   TRY_INIT(dev_alloc(c, &c->d_set_off, table_block_bytes(z.G)));
   c->d_cand_len = c->d_set_off + (z.G + 2);
   c->d_row_start = c->d_cand_len + (z.G + 2);
@@ -1838,7 +1840,8 @@ struct PrefillRun {
     if (sel_counts) sel_counts[l] = m;
     if (sel_groups)
       for (int i = 0; i < m; ++i) sel_groups[(size_t)l * pi.G + i] = cur[i];
-    keep_status st = stage_layer(c, p, pi, l, cur.data(), m, kl, vl, host_kv, &plan);
+    // (without memories, as in the caching of units, the tables of every layer are those of the first)
+    keep_status st = stage_layer(c, p, pi, l, cur.data(), m, kl, vl, host_kv, &plan, pi.G == 0 && l > 0);
     if (st != KEEP_OK) return st;
     if (report) {
       report->rows[l] = plan.n_rows;

@@ -124,11 +124,14 @@ struct GemmB {
 // ---------------------------------------------------------------------------
 // launchers (every one validates nothing: api.hip checks shapes first)
 // ---------------------------------------------------------------------------
-// rows bookkeeping: row_pos[n_rows], row_slot[n_rows] from the set
-void launch_build_rows(const int32_t* d_set_off /*[m] global offset of each selected group*/,
-                       const int32_t* d_row_start /*[m+2] compact prefix, last two: instr start, n_rows*/,
-                       int32_t m, int32_t instr_off, int32_t n_rows, int32_t* d_row_pos, int32_t* d_row_slot,
-                       hipStream_t s);
+// where the recomputed rows sit in the prompt: row_pos[n_rows] from the set
+struct RowMap {
+  const int32_t* set_off;    // [m] global offset of each selected group
+  const int32_t* row_start;  // [m+2] compact prefix, last two: instr start, n_rows
+  int32_t m, instr_off;
+  int32_t* row_pos;          // written
+};
+void launch_build_rows(const RowMap& map, int32_t n_rows, hipStream_t s);
 
 template <typename T>
 void launch_embed_gather(const T* embed, const int32_t* d_token_ids /*[N]*/, const int32_t* d_row_pos,
@@ -141,7 +144,8 @@ void launch_realign(const RealignSeg* d_segs, int32_t n_segs, int32_t total_rows
                     int32_t head_dim, const float* rope_cos, const float* rope_sin, T* k_cache, T* v_cache,
                     hipStream_t s);
 template <typename T>
-void launch_rmsnorm(const T* x, const T* w, int32_t n_rows, int32_t hidden, float eps, T* y, hipStream_t s);
+void launch_rmsnorm(const T* x, const T* w, int32_t n_rows, int32_t hidden, float eps, T* y, hipStream_t s,
+                    const RowMap* map = nullptr);  // map: the rows' positions are written too
 // bias + RoPE + write q/k/v compact + scatter K,V into the cache rows row_pos[]
 template <typename T>
 void launch_rope_scatter(const float* qkv_raw /*[n_rows, q_dim + 2 kv_dim]*/, const T* bq, const T* bk, const T* bv,

@@ -57,24 +57,22 @@ __device__ inline int find_block(const int32_t* starts, int n_blocks, int row) {
 }
 
 // ---------------------------------------------------------------------------
-// positions and block slots of the recomputed rows
+// positions of the recomputed rows
 // ---------------------------------------------------------------------------
-__global__ void k_build_rows(const int32_t* __restrict__ set_off, const int32_t* __restrict__ row_start, int m,
-                             int instr_off, int n_rows, int32_t* __restrict__ row_pos,
-                             int32_t* __restrict__ row_slot) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n_rows) return;
-  int slot = find_block(row_start, m + 1, r);
-  int base = slot < m ? set_off[slot] : instr_off;
-  row_pos[r] = base + (r - row_start[slot]);
-  row_slot[r] = slot;
+__device__ __forceinline__ void put_row_pos(const RowMap& map, int r) {
+  const int slot = find_block(map.row_start, map.m + 1, r);
+  const int base = slot < map.m ? map.set_off[slot] : map.instr_off;
+  map.row_pos[r] = base + (r - map.row_start[slot]);
 }
 
-void launch_build_rows(const int32_t* d_set_off, const int32_t* d_row_start, int32_t m, int32_t instr_off,
-                       int32_t n_rows, int32_t* d_row_pos, int32_t* d_row_slot, hipStream_t s) {
+__global__ void k_build_rows(RowMap map, int n_rows) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r < n_rows) put_row_pos(map, r);
+}
+
+void launch_build_rows(const RowMap& map, int32_t n_rows, hipStream_t s) {
   if (n_rows <= 0) return;
-  hipLaunchKernelGGL(k_build_rows, dim3((n_rows + 255) / 256), dim3(256), 0, s, d_set_off, d_row_start, m, instr_off,
-                     n_rows, d_row_pos, d_row_slot);
+  hipLaunchKernelGGL(k_build_rows, dim3((n_rows + 255) / 256), dim3(256), 0, s, map, n_rows);
 }
 
 // ---------------------------------------------------------------------------
@@ -216,9 +214,12 @@ __device__ inline float block_sum_256(float v, float* s_red) {
   return t;
 }
 
-template <typename T>
+// MAP: the last wave's first thread also writes its row's position, which saves the launch (4.7 us, the least any
+// kernel takes here) that would do it in front of this one.
+template <typename T, bool MAP>
 __global__ void __launch_bounds__(256) k_rmsnorm(const T* __restrict__ x, const T* __restrict__ w, int hidden, float eps,
-                                                 T* __restrict__ y) {
+                                                 T* __restrict__ y, RowMap map) {
+  if (MAP && threadIdx.x == 192) put_row_pos(map, blockIdx.x);
   constexpr int VN = Vec<T>::N;
   __shared__ float s_red[4];
   const size_t base = (size_t)blockIdx.x * hidden;
@@ -243,9 +244,16 @@ __global__ void __launch_bounds__(256) k_rmsnorm(const T* __restrict__ x, const 
 }
 
 template <typename T>
-void launch_rmsnorm(const T* x, const T* w, int32_t n_rows, int32_t hidden, float eps, T* y, hipStream_t s) {
+void launch_rmsnorm(const T* x, const T* w, int32_t n_rows, int32_t hidden, float eps, T* y, hipStream_t s,
+                    const RowMap* map) {
   if (n_rows <= 0) return;
-  hipLaunchKernelGGL(k_rmsnorm<T>, dim3(n_rows), dim3(256), 0, s, x, w, hidden, eps, y);
+  // Up to 2048 rows, the workgroups the chip holds at once, the search for the row's block costs its latency once;
+  // with more it would be paid in every round, and the launch of its own is cheaper.
+  if (map && n_rows > 2048) launch_build_rows(*map, n_rows, s);
+  if (map && n_rows <= 2048)
+    hipLaunchKernelGGL((k_rmsnorm<T, true>), dim3(n_rows), dim3(256), 0, s, x, w, hidden, eps, y, *map);
+  else
+    hipLaunchKernelGGL((k_rmsnorm<T, false>), dim3(n_rows), dim3(256), 0, s, x, w, hidden, eps, y, RowMap{});
 }
 
 // ---------------------------------------------------------------------------
@@ -462,7 +470,7 @@ void launch_argmax(const float* logits, int32_t n, int32_t* out, uint64_t* d_par
                                       hipStream_t);                                                                   \
   template void launch_realign<T>(const RealignSeg*, int32_t, int32_t, int32_t, int32_t, const float*, const float*, \
                                   T*, T*, hipStream_t);                                                               \
-  template void launch_rmsnorm<T>(const T*, const T*, int32_t, int32_t, float, T*, hipStream_t);                     \
+  template void launch_rmsnorm<T>(const T*, const T*, int32_t, int32_t, float, T*, hipStream_t, const RowMap*);      \
   template void launch_rope_scatter<T>(const float*, const T*, const T*, const T*, const int32_t*, int32_t, int32_t, \
                                        int32_t, int32_t, const float*, const float*, T*, T*, T*, T*, hipStream_t,   \
                                        const int32_t*, float*);                                                      \
