@@ -613,17 +613,24 @@ static void launch_cfg(const bf16_t* A, int M, int K, const MfmaB& b, const bf16
 
 size_t gemm_ws_bytes() { return std::max(GEMM_SPLIT_WS_BYTES, gemm_skinny_ws_bytes()); }
 
-// 256x256 tiles (8 waves, 64x128 each) unless the launch is so small that their start-up cost shows
-// (fewer than ~10000 tile K-slices in all); 128x128 tiles then, and where the row counts are not
-// multiples of 256.  A last, partly filled round of workgroups is cut along K in either case.
+// 256x256 tiles (8 waves, 64x128 each) or 128x128 (4 waves, 32x128 each); a last, partly filled round of workgroups is
+// cut along K in either case.  The large tile moves half the operand bytes per flop but fills its last row of tiles
+// less and starts more slowly, so it needs work: tile K slices in all (`work`), rows that fill the tiles, or both.
+// Measured, large / small, in us (hidden 5120 and 3584, rows x K x columns):
+//   at least 10000: always large.  8000 with more than 128 rows: 160 x 3584 x 37888 87 / 90, 384 x 18944 x 3584 69 / 88,
+//   but 128 x 5120 x 27648 83 / 81.  4000 with tiles at least 0.8 full: 512 x 5120 x 7168 55 / 65, 256 x 13824 x 5120
+//   59 / 62, but 300 x 5120 x 7168 45 / 43.  3000 with more than 600 rows: 1024 x 5120 x 5120 65 / 96, 900 x 3584 x 4608
+//   47 / 57, but (2352) 768 x 3584 x 3584 41 / 39.
 static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
   int acc = 0;
   for (int p = 0; p < B.n_parts; ++p) {
     acc += B.n_rows[p];
     if (acc % 256) return false;
   }
-  const long tiles256 = (long)((M + 255) / 256) * (rows / 256);
-  return rows % 256 == 0 && tiles256 * (K / 64) >= 10000;
+  if (rows % 256) return false;
+  const long tiles_m = (M + 255) / 256, work = tiles_m * (rows / 256) * (K / 64);
+  return work >= 10000 || (work >= 8000 && M > 128) || (work >= 4000 && M * 5L >= tiles_m * 256 * 4) ||
+         (work >= 3000 && M > 600);
 }
 
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws) {
@@ -631,7 +638,7 @@ bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool h
   if (have_ws && gemm_skinny_fits(M, K, B, N, EPI_QKV_ROPE)) return true;
   if (have_ws && gemm_skinny_fits(M, K, B, N, EPI_STORE_F32)) return false;
   // every part a whole number of 128-column heads, so that a wave's columns never straddle q / k / v
-  return big_tiles(M, K, B, N) && B.n_rows[0] % 128 == 0 && B.n_rows[1] % 128 == 0 && B.n_rows[2] % 128 == 0;
+  return B.n_rows[0] % 128 == 0 && B.n_rows[1] % 128 == 0 && B.n_rows[2] % 128 == 0;
 }
 
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
@@ -657,7 +664,10 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
   if (big_tiles(M, K, B, rows))
     launch_cfg<256, 256, 4, 2, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
   else if (rows % 128 == 0)
-    launch_cfg<128, 128, 2, 2, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
+    // (a wave as wide as the tile: a head per wave for the fused QKV epilogue, and where weights bound the launch the
+    // waves whose rows lie past M drop out sooner: 64 x 5120 x 5120 20.5 us, 65 x 5120 x 27648 71.6 us, against 20.7
+    // and 73.6 us with 64x64 per wave)
+    launch_cfg<128, 128, 4, 1, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
   else
     launch_cfg<64, 64, 1, 1, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
 }

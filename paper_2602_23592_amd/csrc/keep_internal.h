@@ -196,8 +196,8 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
 // true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows, weight-streaming kernel)
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
 // true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows
-// (weight-streaming kernel) and launches on 256 x 256 tiles (a wave's 128 columns are one head); elsewhere the
-// caller projects to fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel.
+// (weight-streaming kernel) and launches on tiles with 128 columns per wave (one head), which are all where each part's
+// width is a multiple of 128; elsewhere the caller projects to fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel.
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // bf16 expansion of an INT4 matrix: out[rows, K] = bf16((code - zero) * scale)
 void launch_dequant_int4(const void* codes, const void* scale_zero, int32_t rows, int32_t K, void* out, hipStream_t s);
