@@ -238,7 +238,7 @@ keep_status keep_select_groups(keep_ctx* ctx, const float* S, const int32_t* gro
 /* keep_select_groups for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It needs no context: the scratch that the selection uses
  * beyond its inputs and outputs (the candidates' lengths and their token total) lives in a device array built
- * into the library (16.25 KiB, held by every GPU the library runs on until the process ends), and the call
+ * into the library (32.5 KiB, held by every GPU the library runs on until the process ends), and the call
  * makes no allocation, on the device or through any library.  Inputs and outputs are DEVICE memory:
  *   S:         DEVICE [(n_sel + 1) * n_sel], last row the query (as keep_select_groups, but on the device).
  *   groups:    DEVICE [n_sel], strictly ascending group ids below n_groups_total (not checked; ids are clamped

@@ -1,5 +1,5 @@
-// Generic (scalar-FMA, fp32-accumulate) kernels: the kernel family used for fp32
-// storage and for shapes the MFMA kernels do not take.  LDS-tiled GEMM, one-row
+// Generic (fp32-accumulate) kernels: the kernel family used for fp32
+// storage and for shapes the bf16 MFMA kernels do not take.  LDS-tiled GEMM, one-row
 // flash-style attention, per-row group-score reduction.
 #include "keep_internal.h"
 
@@ -99,6 +99,131 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same product for fp32 storage on v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation).
+//
+// Small fp32 models are bound by latency: few tiles, each a chain of K slabs.  So a slab is 64 deep, the next one is
+// on its way to registers (16-byte loads) while the present one is multiplied from LDS, and tiles are 32x32 unless
+// 64x64 ones fill the chip twice.  A lane's 16-byte LDS read holds k = 4 (lane / 16) .. + 3 of its row, one element
+// per MFMA: both operands permute k alike.  Rows are padded to 68 floats, so the 16 lanes of a read cover all banks.
+// The 2-layer, 256-wide fp32 prefill of 1088 tokens spent 576 of its 1222 us in the scalar kernel's products; with this
+// one and the vector reads of dot_head below it takes 417 us.
+// ---------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+template <int MI, int EPI>
+__global__ void __launch_bounds__(256)
+    k_gemm_f32(const float* __restrict__ A, int M, int K, BRows B, const float* __restrict__ B2, int N,
+               const float* __restrict__ residual, float* __restrict__ C) {
+  constexpr int BM = 32 * MI, BK = 64, LD = BK + 4;
+  constexpr int NB = EPI == EPI_SWIGLU_STORE ? 2 : 1;  // weight matrices
+  __shared__ __attribute__((aligned(16))) float As[BM][LD];
+  __shared__ __attribute__((aligned(16))) float Bs[NB][BM][LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BM;
+  // staging: 16 threads per row, rows tid / 16 + 16 i
+  constexpr int LPT = BM / 16;
+  const int sr = tid >> 4, sk = (tid & 15) * 4;
+  const float* ap[LPT];
+  const float* bp[NB][LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int m = m0 + sr + 16 * i, n = n0 + sr + 16 * i;
+    ap[i] = m < M ? A + (size_t)m * K : nullptr;
+    const void* base = B.ptr[0];
+    int first = 0;
+    if (B.n_parts > 1 && n >= B.begin[1]) base = B.ptr[1], first = B.begin[1];
+    if (B.n_parts > 2 && n >= B.begin[2]) base = B.ptr[2], first = B.begin[2];
+    bp[0][i] = n < N ? reinterpret_cast<const float*>(base) + (size_t)(n - first) * K : nullptr;
+    if (NB == 2) bp[NB - 1][i] = n < N ? B2 + (size_t)n * K : nullptr;
+  }
+  f32x4 ra[LPT], rb[NB][LPT];
+  auto fetch = [&](int k0) {
+    const int k = k0 + sk;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      ra[i] = ap[i] && k < K ? *reinterpret_cast<const f32x4*>(ap[i] + k) : zero;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) rb[b][i] = bp[b][i] && k < K ? *reinterpret_cast<const f32x4*>(bp[b][i] + k) : zero;
+    }
+  };
+  f32x4 acc[NB][MI][MI];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < MI; ++j) acc[b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int row = lane & 15, kg = lane >> 4;
+  fetch(0);
+  for (int k0 = 0; k0 < K; k0 += BK) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      *reinterpret_cast<f32x4*>(&As[sr + 16 * i][sk]) = ra[i];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) *reinterpret_cast<f32x4*>(&Bs[b][sr + 16 * i][sk]) = rb[b][i];
+    }
+    __syncthreads();
+    if (k0 + BK < K) fetch(k0 + BK);
+#pragma unroll
+    for (int c = 0; c < BK / 16; ++c) {
+      f32x4 a[MI], w[NB][MI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        a[i] = *reinterpret_cast<const f32x4*>(&As[(wm * MI + i) * 16 + row][c * 16 + kg * 4]);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          w[b][i] = *reinterpret_cast<const f32x4*>(&Bs[b][(wn * MI + i) * 16 + row][c * 16 + kg * 4]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < MI; ++j)
+              acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], w[b][j][e], acc[b][i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  // acc[..][i][j][e]: row 4 (lane / 16) + e, column lane % 16 of the 16x16 tile
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = m0 + (wm * MI + i) * 16 + 4 * kg + e;
+      if (m >= M) continue;
+#pragma unroll
+      for (int j = 0; j < MI; ++j) {
+        const int n = n0 + (wn * MI + j) * 16 + row;
+        if (n >= N) continue;
+        const size_t idx = (size_t)m * N + n;
+        const float v = acc[0][i][j][e];
+        if (EPI == EPI_STORE_F32)
+          C[idx] = v;
+        else if (EPI == EPI_RESIDUAL_STORE)
+          C[idx] = residual[idx] + v;
+        else
+          C[idx] = v / (1.0f + expf(-v)) * acc[NB - 1][i][j][e];
+      }
+    }
+}
+
+template <int EPI>
+static void launch_gemm_f32(const float* A, int M, int K, const BRows& br, const float* B2, int N, const float* residual,
+                            float* C, hipStream_t s) {
+  const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+  if (tiles64 >= 512)
+    hipLaunchKernelGGL((k_gemm_f32<2, EPI>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, A, M, K, br, B2, N,
+                       residual, C);
+  else
+    hipLaunchKernelGGL((k_gemm_f32<1, EPI>), dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, s, A, M, K, br, B2, N,
+                       residual, C);
+}
+
 template <typename T>
 void launch_gemm_generic(const T* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                          const T* residual, void* C, hipStream_t s) {
@@ -114,6 +239,21 @@ void launch_gemm_generic(const T* A, int32_t M, int32_t K, const GemmB& B, const
   br.begin[3] = acc;
   dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
   const T* b2 = reinterpret_cast<const T*>(B2);
+  if constexpr (sizeof(T) == 4) {
+    // 16-byte loads along K: whole vectors, aligned rows
+    uintptr_t at = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B2);
+    for (int p = 0; p < B.n_parts; ++p) at |= reinterpret_cast<uintptr_t>(B.ptr[p]);
+    if (K % 4 == 0 && at % 16 == 0) {
+      float* c = reinterpret_cast<float*>(C);
+      if (epilogue == EPI_STORE_F32)
+        launch_gemm_f32<EPI_STORE_F32>(A, M, K, br, b2, N, residual, c, s);
+      else if (epilogue == EPI_RESIDUAL_STORE)
+        launch_gemm_f32<EPI_RESIDUAL_STORE>(A, M, K, br, b2, N, residual, c, s);
+      else
+        launch_gemm_f32<EPI_SWIGLU_STORE>(A, M, K, br, b2, N, residual, c, s);
+      return;
+    }
+  }
   switch (epilogue) {
     case EPI_STORE_F32:
       hipLaunchKernelGGL((k_gemm_generic<T, EPI_STORE_F32>), grid, block, 0, s, A, M, K, br, b2, N, residual, C);
@@ -125,6 +265,28 @@ void launch_gemm_generic(const T* A, int32_t M, int32_t K, const GemmB& B, const
       hipLaunchKernelGGL((k_gemm_generic<T, EPI_SWIGLU_STORE>), grid, block, 0, s, A, M, K, br, b2, N, residual, C);
       break;
   }
+}
+
+// q (LDS) . k (one head of one cache row), summed in ascending order.  A lane reads its own row, so what bounds the
+// loop is the number of load instructions: fp32 heads of whole 16-byte vectors (the kernels that write the rows store
+// such vectors) are read four elements at a time.
+template <typename T>
+__device__ __forceinline__ float dot_head(const float* q, const T* __restrict__ k, int head_dim) {
+  float dot = 0.f;
+  if constexpr (sizeof(T) == 4) {
+    if (head_dim % 16 == 0) {
+      for (int d = 0; d < head_dim; d += 16) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(k + d + 4 * u);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) dot += q[d + u] * v[u / 4][u % 4];
+      }
+      return dot;
+    }
+  }
+  for (int d = 0; d < head_dim; ++d) dot += q[d] * ldf(k + d);
+  return dot;
 }
 
 // ---------------------------------------------------------------------------
@@ -160,9 +322,7 @@ __global__ void __launch_bounds__(256)
     float sc = -INFINITY;
     if (key <= p_row) {
       const T* kr = k_cache + (size_t)key * kv_dim + hk * head_dim;
-      float dot = 0.f;
-      for (int d = 0; d < head_dim; ++d) dot += s_q[d] * ldf(kr + d);
-      sc = dot * scale;
+      sc = dot_head(s_q, kr, head_dim) * scale;
     }
     // chunk max
     float mx = sc;
@@ -184,6 +344,7 @@ __global__ void __launch_bounds__(256)
     if (pv_active) {
       acc *= alpha;
       const int kmax = min(256, p_row + 1 - c0);
+#pragma unroll 8
       for (int j = part; j < kmax; j += n_parts)
         acc += s_p[j] * ldf(v_cache + (size_t)(c0 + j) * kv_dim + hk * head_dim + d_out);
     }
@@ -254,9 +415,7 @@ __global__ void __launch_bounds__(256)
         for (int h = 0; h < n_q_heads; ++h) {
           const T* kh = kr + (h / rep) * head_dim;
           const float* qh = s_q + h * head_dim;
-          float dot = 0.f;
-          for (int d = 0; d < head_dim; ++d) dot += qh[d] * ldf(kh + d);
-          sum += expf(dot * scale - s_lse[h]);
+          sum += expf(dot_head(qh, kh, head_dim) * scale - s_lse[h]);
         }
       }
     }

@@ -198,7 +198,7 @@ __device__ int compact(const uint8_t* taken, int m, int32_t* list, int* s_cnt /*
 // (0 where the row is empty); it is formed where it is used, only the row totals are kept.
 //
 // Bound by its chain of small steps.  It reads only the rows of S that the propagation averages, 16 loads in flight per
-// thread.  1024 candidates, 307 kept, three selections: 118 us; one workgroup that also summed the rows, ranked every
+// thread.  1024 candidates, 308 kept, three selections: 118 us; one workgroup that also summed the rows, ranked every
 // candidate against every other and walked budget and output list one by one took 1020 us.
 __global__ void __launch_bounds__(SEL_THREADS)
     k_select(const float* __restrict__ S, int m, int P, const int32_t* __restrict__ cand_len, int k_count,
