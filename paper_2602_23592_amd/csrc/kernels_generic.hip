@@ -107,7 +107,8 @@ __global__ void __launch_bounds__(256)
 // 64x64 ones fill the chip twice.  A lane's 16-byte LDS read holds k = 4 (lane / 16) .. + 3 of its row, one element
 // per MFMA: both operands permute k alike.  Rows are padded to 68 floats, so the 16 lanes of a read cover all banks.
 // The 2-layer, 256-wide fp32 prefill of 1088 tokens spent 576 of its 1222 us in the scalar kernel's products; with this
-// one and the vector reads of dot_head below it takes 417 us.
+// one and the vector reads of dot_head below it takes 417 us.  Its caches' error against 64 bits is unchanged (3.0e-7 and
+// 3.4e-7 in the 2-norm at the two layers, with either kernel).
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
