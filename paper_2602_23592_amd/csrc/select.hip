@@ -4,8 +4,9 @@
 // Every floating-point value that decides the selection is computed in binary32 in a fixed order (sums over
 // candidates in ascending order, one division each), so the result is a pure function of S.
 //
-// Two kernels: k_row_totals (many workgroups: reading S once needs more than one CU) and k_select (one workgroup:
-// what is left is a chain of small steps that depend on each other).
+// From 64 candidates on two kernels: k_row_totals (many workgroups: reading S once needs more than one CU) and k_select
+// (one workgroup: what is left is a chain of small steps that depend on each other).  Below, one wave does all of it
+// (k_select_small).
 #include "keep_internal.h"
 
 namespace keep {
@@ -129,12 +130,33 @@ __device__ void sel_sort(uint64_t* key, int P) {
   __syncthreads();
 }
 
+// A walk of up to 64 memories in rank order, one per lane: the ones that still fit, as a mask; `left` shrinks by them.
+// Of those that fit what is left, all up to the first whose running sum does not are taken at once, that one is passed
+// over, and so on; what does not fit once never will.
+__device__ __forceinline__ uint64_t walk_chunk(bool valid, int l, int lane, int& left) {
+  uint64_t cand = __ballot(valid && l <= left), got = 0;
+  while (cand) {
+    int64_t sum = cand >> lane & 1 ? l : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t t = __shfl_up((long long)sum, o, 64);
+      if (lane >= o) sum += t;
+    }
+    const uint64_t over = __ballot((cand >> lane & 1) && sum > left);
+    const int f = over ? __builtin_ctzll(over) : 64;  // the first that does not fit behind those before it
+    got |= f < 64 ? cand & ((1ull << f) - 1) : cand;
+    if (f > 0) left -= (int)__shfl((long long)sum, f - 1, 64);
+    cand = f < 63 ? cand & ~((2ull << f) - 1) : 0;
+    cand &= __ballot(l <= left);
+  }
+  return got;
+}
+
 // Mark what is taken of the order: its first k (count mode) or a walk of it that takes a memory iff it still fits the
 // token budget (token mode).  key[b], b < m: the candidates' keys.
 //
 // Ranking by sorting: 1024 candidates against each other are 2^20 comparisons for one CU, the sort is 55 short steps.
-// The walk goes in chunks of 64 through one wave: of those that fit what is left, all up to the first whose running
-// sum does not are taken at once, that one is passed over, and so on; what does not fit once never will.
+// The walk goes in chunks of 64 through one wave.
 __device__ void take(uint64_t* key, int m, int P, const int32_t* len, int k_count, int token_budget, int mode,
                      uint8_t* taken) {
   for (int b = m + threadIdx.x; b < P; b += SEL_THREADS) key[b] = ~0ull;
@@ -151,22 +173,7 @@ __device__ void take(uint64_t* key, int m, int P, const int32_t* len, int k_coun
     for (int c0 = 0; c0 < m; c0 += 64) {
       const bool valid = c0 + lane < m;
       const int b = valid ? (int)(uint32_t)key[c0 + lane] : 0;
-      const int l = valid ? len[b] : 0;
-      uint64_t cand = __ballot(valid && l <= left), got = 0;
-      while (cand) {
-        int64_t sum = cand >> lane & 1 ? l : 0;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int64_t t = __shfl_up((long long)sum, o, 64);
-          if (lane >= o) sum += t;
-        }
-        const uint64_t over = __ballot((cand >> lane & 1) && sum > left);
-        const int f = over ? __builtin_ctzll(over) : 64;  // the first that does not fit behind those before it
-        got |= f < 64 ? cand & ((1ull << f) - 1) : cand;
-        if (f > 0) left -= (int)__shfl((long long)sum, f - 1, 64);
-        cand = f < 63 ? cand & ~((2ull << f) - 1) : 0;
-        cand &= __ballot(l <= left);
-      }
+      const uint64_t got = walk_chunk(valid, valid ? len[b] : 0, lane, left);
       if (valid) taken[b] = got >> lane & 1;
     }
   }
@@ -284,15 +291,111 @@ __global__ void __launch_bounds__(SEL_THREADS)
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// k_select_small: fewer than 64 candidates, one per lane of one wave.
+//
+// Bound by launches and barriers.  Four waves bring S (at most 64 x 63) to LDS, all loads in flight at once, and the
+// first goes on alone, without a barrier: sets are 64-bit masks, ranks are counted.  The same sums, divisions and orders
+// as in k_row_totals and k_select, so the same sets.  One wave holds up to 63 candidates and the query's row; from 64 on
+// the two kernels above take over.  A call that is waited for, up to four selections: 9 candidates 22 us (36 with the two
+// kernels), 63 candidates 37 us (64 with the two kernels: 51).
+// ---------------------------------------------------------------------------------------------
+constexpr int SEL_SMALL = 64;  // rows of S
+
+__global__ void __launch_bounds__(256)
+    k_select_small(const float* __restrict__ S, int m, const int32_t* __restrict__ cand_len, int k_count,
+                   int token_budget, int mode, int hops, int set_only, int32_t* __restrict__ out, SelectPrep prep) {
+  __shared__ float s_S[SEL_SMALL][SEL_SMALL + 1];
+  __shared__ uint64_t s_key[SEL_SMALL];
+  __shared__ int s_at[SEL_SMALL];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool valid = lane < m;
+  const bool classify = prep.cand_total;  // candidates given as indices, budget not classified by the caller
+  {
+    float v[SEL_SMALL / 4];
+#pragma unroll
+    for (int u = 0; u < SEL_SMALL / 4; ++u) v[u] = valid && wave + 4 * u <= m ? S[(size_t)(wave + 4 * u) * m + lane] : 0.f;
+#pragma unroll
+    for (int u = 0; u < SEL_SMALL / 4; ++u) s_S[wave + 4 * u][lane] = v[u];
+  }
+  int len = 0;
+  if (wave == 0 && valid)
+    len = classify ? prep.group_len[min(max(prep.groups[lane], 0), prep.n_groups - 1)] : cand_len[lane];
+  __syncthreads();
+  if (wave) return;
+  uint64_t set = 0;
+  int runs = 0;
+  bool all = false, none = false;
+  if (classify) {
+    int sum = len;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    all = m > 0 && (mode == KEEP_BUDGET_GROUP_COUNT ? k_count >= m : token_budget >= sum);
+    none = m == 0 || (mode == KEEP_BUDGET_GROUP_COUNT ? k_count == 0 : token_budget <= 0);
+  }
+  if (all) {
+    set = (1ull << m) - 1;
+  } else if (!none) {
+    float total = 0.f;  // of the lane's row of S; the query's row is row m
+    for (int j = 0; j < m; ++j) total = total + s_S[lane][j];
+    auto choose = [&](float v) -> uint64_t {
+      const uint64_t key = valid ? sel_key(v, lane) : ~0ull;
+      s_key[lane] = key;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      int rank = 0;
+      for (int c = 0; c < m; ++c) rank += s_key[c] < key;
+      bool taken;
+      if (mode == KEEP_BUDGET_GROUP_COUNT) {
+        taken = (uint32_t)(key >> 32) == 0xFFFFFFFFu ? k_count > 0 : rank < k_count;  // (a NaN: as in take)
+      } else {
+        if (valid) s_at[rank] = lane;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int l = __shfl(len, valid ? s_at[lane] : 0, 64);
+        int left = token_budget;
+        taken = walk_chunk(valid, l, lane, left) >> rank & 1;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      return __ballot(valid && taken);
+    };
+    const float tq = __shfl(total, m, 64);
+    const float query = tq > 0.f ? s_S[m][lane] / tq : 0.f;
+    set = choose(query);
+    runs = 1;
+    while (runs < hops) {
+      const int n_src = (set_only ? 0 : 1) + __popcll(set);
+      float acc = set_only ? 0.f : query;
+      for (uint64_t a = set; a; a &= a - 1) {
+        const int i = __builtin_ctzll(a);
+        const float ta = __shfl(total, i, 64);
+        acc = acc + (ta > 0.f ? s_S[i][lane] / ta : 0.f);
+      }
+      const uint64_t next = choose(n_src > 0 ? acc / (float)n_src : acc);
+      ++runs;
+      if (next == set) break;
+      set = next;
+    }
+  }
+  if (set >> lane & 1) out[2 + __popcll(set & ((1ull << lane) - 1))] = classify ? prep.groups[lane] : lane;
+  if (lane == 0) {
+    out[0] = __popcll(set);
+    out[1] = runs;
+  }
+}
+
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
                    int32_t mode, int32_t hops, float* d_tot, int32_t* d_out, hipStream_t s, bool set_only,
                    const SelectPrep* prep) {
+  const SelectPrep pr = prep ? *prep : SelectPrep{};
+  if (m < SEL_SMALL) {
+    hipLaunchKernelGGL(k_select_small, dim3(1), dim3(256), 0, s, S, m, d_cand_len, k_count, token_budget, mode, hops,
+                       set_only ? 1 : 0, d_out, pr);
+    return;
+  }
   int P = 2;
   while (P < m) P <<= 1;
   const size_t sh = (size_t)P * 8 + (size_t)m * (3 * 4 + 2);  // <= 147 KB: m <= 6000
   static std::atomic<uint64_t> attr_done{0};
   set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select), 160 * 1024 - 256);
-  const SelectPrep pr = prep ? *prep : SelectPrep{};
   const int blocks = (m + 1 + RT_ROWS - 1) / RT_ROWS + (prep ? 1 : 0);
   hipLaunchKernelGGL(k_row_totals, dim3(blocks), dim3(RT_THREADS), 0, s, S, m, d_tot, pr);
   hipLaunchKernelGGL(k_select, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode, hops,

@@ -38,3 +38,33 @@ def test_selection_edges(ctx, m):
                 want, runs = ko.select_multihop(S, groups, glen, ratio, hops, mode)
                 got, got_runs = ctx.select_groups(S, groups, glen, ratio, hops, mode)
                 assert got == want and got_runs == runs, (m, lens, mode, hops)
+
+
+@pytest.mark.parametrize("m", [1, 2, 4, 9, 17, 40, 62, 63, 64])
+def test_few_candidates(ctx, m):
+    """Around the line below which one wave selects alone, through both entry points, with the query as a source of the
+    propagation and without."""
+    import torch
+    from paper_2602_23592_amd import binding as kb
+    rng = np.random.default_rng(100 + m)
+    G = m + 3
+    for trial in range(6):
+        glen = [int(v) for v in (rng.integers(1, 90, size=G) if trial % 2 else np.exp(rng.uniform(0, 7, size=G)).astype(int) + 1)]
+        groups = sorted(int(v) for v in rng.choice(G, size=m, replace=False))
+        S = np.tril(rng.random((m + 1, m)), -1).astype(np.float32)
+        if trial >= 4:                          # ties, rows without mass, a query that attends to nothing
+            S = (np.round(S * 3) / 3).astype(np.float32)
+            S[m] = 0.0 if trial == 5 else S[m]
+        for sources in (kb.KEEP_SOURCES_QUERY_AND_SET, kb.KEEP_SOURCES_SET_ONLY):
+            ctx.set_option(kb.KEEP_OPT_PROPAGATION_SOURCES, sources)
+            for mode in (kb.KEEP_BUDGET_GROUP_COUNT, kb.KEEP_BUDGET_TOKENS):
+                for hops, ratio in ((1, 0.3), (2, 0.5), (4, 0.15), (9, 0.7), (3, 1.0), (3, 0.0)):
+                    want = ko.select_multihop(S, groups, glen, ratio, hops, mode, sources == kb.KEEP_SOURCES_SET_ONLY)
+                    assert ctx.select_groups(S, groups, glen, ratio, hops, mode) == want, (m, trial, sources, mode, hops)
+                    res = torch.full((m + 3,), -7, dtype=torch.int32, device="cuda")
+                    kb.select_groups_static(torch.from_numpy(S).cuda(), torch.tensor(groups, dtype=torch.int32, device="cuda"),
+                                            torch.tensor(glen, dtype=torch.int32, device="cuda"), sum(glen), ratio, hops,
+                                            mode, sources, res)
+                    out = res.cpu().tolist()
+                    assert (out[2:2 + out[0]], out[1]) == want and out[m + 2] == -7, (m, trial, sources, mode, hops)
+    ctx.set_option(kb.KEEP_OPT_PROPAGATION_SOURCES, kb.KEEP_SOURCES_QUERY_AND_SET)
