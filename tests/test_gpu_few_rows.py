@@ -9,6 +9,7 @@ import keep_synth as ks
 from oracle import keep_oracle as ko
 from gpu_util import Problem, max_rel, to_np
 from test_gpu_decode import head_weights
+from test_gpu_int4 import Int4Problem
 
 pytestmark = pytest.mark.gpu
 
@@ -16,12 +17,27 @@ pytestmark = pytest.mark.gpu
 # activations beyond the two vectors a thread keeps in registers) with tiles of 9 units
 NARROW = ks.ModelShape(2, 448, 7, 1, 128, 1344, 1031, 1.0e6, 1e-6, "bf16")
 WIDE = ks.ModelShape(2, 8256, 2, 1, 128, 320, 211, 1.0e6, 1e-6, "bf16")
+# an FFN wide enough that workgroups own tiles of 17 units (two MFMA tiles, and on the 4-bit form rows of two storage
+# blocks) and more than one of them, and so many heads that a QKV tile holds 16 column pairs; and the same for the output
+# and down projections
+FAN = ks.ModelShape(2, 512, 28, 4, 128, 8320, 211, 1.0e6, 1e-6, "bf16")
+WIDE4 = ks.ModelShape(2, 8320, 2, 1, 128, 384, 211, 1.0e6, 1e-6, "bf16")
 
 
-@pytest.mark.parametrize("shape", [NARROW, WIDE], ids=["narrow", "wide"])
-@pytest.mark.parametrize("n", [1, 2, 15, 16, 17])
-def test_few_rows_match_oracle(shape, n):
+def _odd(t):
+    """The same matrix at an address that is no multiple of 4 bytes."""
+    return torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t)
+
+
+@pytest.mark.parametrize("shape,n,aligned", [(s, n, True) for s in (NARROW, WIDE) for n in (1, 2, 15, 16, 17)] +
+                         [(FAN, n, True) for n in (1, 2, 9, 16)] + [(FAN, n, False) for n in (1, 9)],
+                         ids=lambda v: "h%d" % v.hidden if isinstance(v, ks.ModelShape) else str(v))
+def test_few_rows_match_oracle(shape, n, aligned):
     pb = Problem(shape, [n], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)
+    if not aligned:
+        for w in pb.layers_d:
+            for name in ks.INT4_MATS:           # the seven projections
+                w[name] = _odd(w[name])
     ctx = pb.context(max_tokens=n + 2)
     assert ctx.uses_mfma
     L = shape.n_layers
@@ -41,7 +57,7 @@ def test_few_rows_match_oracle(shape, n):
     fn, lm = head_weights(shape)
     x = torch.randn(shape.hidden, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
     lg = torch.empty((2, shape.vocab), dtype=torch.float32, device="cuda")
-    toks = ctx.decode(fn.cuda(), lm.cuda(), x.cuda(), kc, vc, n, 2, logits_out=lg)
+    toks = ctx.decode(fn.cuda(), lm.cuda() if aligned else _odd(lm), x.cuda(), kc, vc, n, 2, logits_out=lg)
     pad = lambda rows: [np.concatenate([r[0], np.zeros((1,) + r[0].shape[1:])]) for r in rows]
     kr, vr = pad(pb.kb), pad(pb.vb)
     _, ref = ko.greedy_decode(pb.sh, pb.layers, pb.embed, ks.to_numpy_f64(fn), ks.to_numpy_f64(lm), ks.to_numpy_f64(x),
@@ -50,5 +66,34 @@ def test_few_rows_match_oracle(shape, n):
         e = max_rel(to_np(lg)[t], ref[t])
         print(n, "token", t, "logits %.2e" % e)
         assert e < 2e-2
+    for l in range(L):
+        assert max_rel(to_np(kc[l, n]), kr[l][n]) < 2e-2 and max_rel(to_np(vc[l, n]), vr[l][n]) < 2e-2
+
+
+@pytest.mark.parametrize("shape", [FAN, WIDE4], ids=lambda v: "h%d" % v.hidden)
+@pytest.mark.parametrize("n", [1, 2, 9, 16, 17])
+def test_few_rows_int4_match_oracle(shape, n):
+    """The same on the 4-bit form of the projections (17 rows: the kernel behind the line)."""
+    pb = Int4Problem(shape, std=0.5 / np.sqrt(shape.hidden), seed=n)
+    L = shape.n_layers
+    ids = ks.make_token_ids(n, shape.vocab, n)
+    ctx = pb.context(n + 2, 1)
+    k, v = (torch.zeros((L, n, shape.n_kv_heads, shape.head_dim), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ctx.precompute_group(ids, k, v)
+    kb, vb = ko.precompute_group_caches(pb.sh, pb.layers, pb.embed, ids, [n])
+    for l in range(L):
+        ek, ev = max_rel(to_np(k[l]), kb[l][0]), max_rel(to_np(v[l]), vb[l][0])
+        print(n, "layer", l, "K %.2e V %.2e" % (ek, ev))
+        assert ek < 2e-2 and ev < 2e-2
+    # one token decoded behind the unit
+    x = torch.randn(shape.hidden, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
+    kc, vc = (torch.cat([t, torch.zeros_like(t[:, :1])], dim=1) for t in (k, v))
+    kr, vr = ([to_np(t[l]) for l in range(L)] for t in (kc, vc))
+    lg = torch.empty((2, shape.vocab), dtype=torch.float32, device="cuda")
+    toks = ctx.decode(pb.fn_t.cuda(), pb.lm_t.cuda(), x.cuda(), kc, vc, n, 2, logits_out=lg)
+    _, ref = ko.greedy_decode(pb.sh, pb.layers, pb.embed, ks.to_numpy_f64(pb.fn_t), ks.to_numpy_f64(pb.lm_t),
+                              ks.to_numpy_f64(x), kr, vr, n, 2, forced_tokens=toks)
+    for t in range(2):
+        assert max_rel(to_np(lg)[t], ref[t]) < 2e-2
     for l in range(L):
         assert max_rel(to_np(kc[l, n]), kr[l][n]) < 2e-2 and max_rel(to_np(vc[l, n]), vr[l][n]) < 2e-2
