@@ -68,3 +68,46 @@ def test_few_candidates(ctx, m):
                     out = res.cpu().tolist()
                     assert (out[2:2 + out[0]], out[1]) == want and out[m + 2] == -7, (m, trial, sources, mode, hops)
     ctx.set_option(kb.KEEP_OPT_PROPAGATION_SOURCES, kb.KEEP_SOURCES_QUERY_AND_SET)
+
+
+@pytest.mark.parametrize("m", [9, 63, 64, 300])
+def test_an_infinite_score(ctx, m):
+    """An infinite score makes its candidate's importance inf / inf and every other one zero.  No importance is greater
+    than a NaN, so the count budget takes the candidate beside the others' first k (ties by index); the token walk comes
+    to it last."""
+    rng = np.random.default_rng(m)
+    glen = [int(v) for v in rng.integers(1, 9, size=m)]
+    for b in (0, m // 2, m - 1):
+        S = np.tril(rng.random((m + 1, m)), -1).astype(np.float32)
+        S[m, b] = np.inf
+        others = [i for i in range(m) if i != b]
+        for ratio in (0.1, 0.6):
+            got, _ = ctx.select_groups(S, list(range(m)), glen, ratio, 1, 0)
+            assert got == sorted(others[:ko.budget_count(ratio, m, m)] + [b]), (m, b, ratio)
+            left, want = ko.budget_tokens(ratio, sum(glen)), []
+            for i in others + [b]:
+                if glen[i] <= left:
+                    want.append(i)
+                    left -= glen[i]
+            assert ctx.select_groups(S, list(range(m)), glen, ratio, 1, 1)[0] == sorted(want), (m, b, ratio)
+
+
+def test_most_candidates():
+    """4096 candidates through the entry point that allocates nothing, 6000 through a context: the most either takes."""
+    import torch
+    from paper_2602_23592_amd import binding as kb
+    shape = ks.ModelShape(2, 64, 4, 2, 16, 96, 97, 1.0e4, 1e-6, "f32")
+    big = Problem(shape, [4] * 8, 2, seed=2, random_cache=True).context(max_groups=6000)
+    for m, mode in ((4096, 1), (6000, 0)):
+        rng = np.random.default_rng(m)
+        glen = [int(v) for v in rng.integers(1, 200, size=m)]
+        S = np.tril(rng.random((m + 1, m), dtype=np.float32), -1)
+        want = ko.select_multihop(S, list(range(m)), glen, 0.2, 2, mode)
+        print(m, len(want[0]), "kept", flush=True)
+        assert big.select_groups(S, list(range(m)), glen, 0.2, 2, mode) == want
+        if m == 4096:
+            res = torch.zeros(m + 2, dtype=torch.int32, device="cuda")
+            ids, lens = (torch.tensor(v, dtype=torch.int32, device="cuda") for v in (list(range(m)), glen))
+            kb.select_groups_static(torch.from_numpy(S).cuda(), ids, lens, sum(glen), 0.2, 2, mode, 0, res)
+            out = res.cpu().tolist()
+            assert (out[2:2 + out[0]], out[1]) == want
