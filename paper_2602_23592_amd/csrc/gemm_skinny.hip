@@ -508,15 +508,17 @@ static void launch_gemv_rows(const GemvArgs& g, int epilogue, hipStream_t s) {
     launch_gemv_cfg<EPI_STORE_F32, 1, ONE_ROW, W4>(g, s);
 }
 
-// Rows, K and the parts' widths k_gemv takes.  (A row of up to 64 KB of activations in LDS leaves room for two
-// workgroups per CU; longer rows, beyond any model here, take one.)
+// Rows, K and the parts' widths k_gemv takes (32-bit offsets into a tile of weight rows bound K, beyond any model).
 static bool gemv_fits(int32_t M, int32_t K, const GemmB& B) {
-  if (M < 1 || M > GV_MAX_ROWS || K % 64 || (M == 1 && (size_t)K * 2 + 8192 > (size_t)GV_MAX_LDS)) return false;
-  if ((size_t)16 * K * 2 >= GV_PAST_END) return false;
+  if (M < 1 || M > GV_MAX_ROWS || K % 64 || (size_t)16 * K * 2 >= GV_PAST_END) return false;
   for (int p = 0; p + 1 < B.n_parts; ++p)
     if (B.n_rows[p] % 16) return false;
   return true;
 }
+
+// A single row is kept in LDS where it fits beside the partial sums (up to 64 KB of it leave room for two workgroups per
+// CU); a longer one is read like several rows, by every wave for itself.
+static bool gemv_row_in_lds(int32_t M, int32_t K) { return M == 1 && (size_t)K * 2 + 8192 <= (size_t)GV_MAX_LDS; }
 
 struct SkinnyW4 {
   const uint8_t* codes[3];
@@ -671,11 +673,11 @@ bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
   // bf16 weights the matrix-core tiles are faster from 17 rows on; the 4-bit form moves a quarter of the bytes and
   // wins up to 48 rows (33 rows: 7.3 ms against 8.4 ms, 48: 8.5 against 8.6, 64: 9.5 against 8.8).
   if (gemv_fits(M, K, B)) return true;
-  return B.has_w4 && M >= 1 && M <= 48 && epilogue != EPI_QKV_ROPE && (size_t)M * (size_t)ld <= SK_MAX_PART_FLOATS;
+  return B.has_w4 && M > GV_MAX_ROWS && M <= 48 && epilogue != EPI_QKV_ROPE && (size_t)M * (size_t)ld <= SK_MAX_PART_FLOATS;
 }
 
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws) {
-  return have_ws && M == 1 && gemv_fits(M, K, B) && gemm_skinny_fits(M, K, B, N, epilogue);
+  return have_ws && gemv_row_in_lds(M, K) && gemv_fits(M, K, B) && gemm_skinny_fits(M, K, B, N, epilogue);
 }
 
 void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
@@ -708,10 +710,11 @@ void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, c
     g.residual = residual;
     g.C = C;
     if (qkv) g.qe = *qkv;
+    const bool one_row = gemv_row_in_lds(M, K);
     if (B.has_w4)
-      M == 1 ? launch_gemv_rows<true, true>(g, epilogue, s) : launch_gemv_rows<false, true>(g, epilogue, s);
+      one_row ? launch_gemv_rows<true, true>(g, epilogue, s) : launch_gemv_rows<false, true>(g, epilogue, s);
     else
-      M == 1 ? launch_gemv_rows<true, false>(g, epilogue, s) : launch_gemv_rows<false, false>(g, epilogue, s);
+      one_row ? launch_gemv_rows<true, false>(g, epilogue, s) : launch_gemv_rows<false, false>(g, epilogue, s);
     return;
   }
   // 17 to 48 rows, 4-bit form

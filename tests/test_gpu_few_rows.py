@@ -97,3 +97,30 @@ def test_few_rows_int4_match_oracle(shape, n):
         assert max_rel(to_np(lg)[t], ref[t]) < 2e-2
     for l in range(L):
         assert max_rel(to_np(kc[l, n]), kr[l][n]) < 2e-2 and max_rel(to_np(vc[l, n]), vr[l][n]) < 2e-2
+
+
+@pytest.mark.parametrize("form", ["bf16", "int4"])
+@pytest.mark.parametrize("hidden", [76800, 76928])
+def test_longest_row_in_lds_and_longer(form, hidden):
+    """One decoded token at the longest row of activations that fits LDS and at the next longer one, with a vocabulary
+    that fills no last tile."""
+    shape = ks.ModelShape(1, hidden, 1, 1, 128, 128, 97, 1.0e6, 1e-6, "bf16")
+    std = 0.5 / np.sqrt(hidden)
+    if form == "int4":
+        pb = Int4Problem(shape, std=std)
+        ctx, fn, lm = pb.context(4, 1), pb.fn_t, pb.lm_t
+    else:
+        pb = Problem(shape, [2], 1, std=std)
+        ctx = pb.context(max_tokens=4)
+        fn, lm = head_weights(shape)
+    g = torch.Generator().manual_seed(2)
+    x = torch.randn(hidden, generator=g).to(torch.bfloat16)
+    kc, vc = (torch.randn((1, 4, 1, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    kr, vr = [to_np(kc[0])], [to_np(vc[0])]
+    lg = torch.full((2, shape.vocab), float("nan"), dtype=torch.float32, device="cuda")
+    toks = ctx.decode(fn.cuda(), lm.cuda(), x.cuda(), kc, vc, 2, 2, logits_out=lg)
+    _, ref = ko.greedy_decode(pb.sh, pb.layers, pb.embed, ks.to_numpy_f64(fn), ks.to_numpy_f64(lm), ks.to_numpy_f64(x),
+                              kr, vr, 2, 2, forced_tokens=toks)
+    for t in range(2):
+        assert max_rel(to_np(lg)[t], ref[t]) < 2e-2
+    assert max_rel(to_np(kc[0, 2]), kr[0][2]) < 2e-2 and max_rel(to_np(vc[0, 2]), vr[0][2]) < 2e-2
