@@ -745,21 +745,16 @@ keep_status decode_impl(keep_ctx* c, const void* final_norm, const void* lm_head
         set_w4(b, 2, c->w4[l].wv);
       }
       const int n_qkv = b.n_rows[0] + 2 * b.n_rows[1];
-      const bool fuse_qkv = c->mfma && gemm_mfma_fuses_qkv(1, d.hidden, b, n_qkv, c->skinny_ws != nullptr);
-      const bool fuse_norm = fuse_qkv && gemm_fuses_norm(1, d.hidden, b, n_qkv, EPI_QKV_ROPE, c->skinny_ws != nullptr);
+      const bool fuse_norm = c->mfma && gemm_fuses_norm(1, d.hidden, b, n_qkv, EPI_QKV_ROPE, c->skinny_ws != nullptr);
       if (!fuse_norm)
         launch_rmsnorm<T>(Typed<T>::p(x_cur), Typed<T>::p(w.ln1), 1, d.hidden, d.rms_eps, Typed<T>::p(c->hbuf), s);
-      if (fuse_qkv) {
+      if (c->mfma) {  // (one row always has the fused epilogue)
         const QkvEpilogue qe = qkv_epilogue(c, w, b, d_pos, nullptr, kl, vl);
         const RowNorm norm{w.ln1, d.rms_eps};
         launch_gemm_mfma(reinterpret_cast<const bf16_t*>(fuse_norm ? x_cur : c->hbuf), 1, d.hidden, b, nullptr, n_qkv,
                          EPI_QKV_ROPE, nullptr, nullptr, s, c->skinny_ws, &qe, fuse_norm ? &norm : nullptr);
       } else {
-        if (c->mfma)
-          launch_gemm_mfma(reinterpret_cast<const bf16_t*>(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32,
-                           nullptr, c->qkv_raw, s, c->skinny_ws);
-        else
-          launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32, nullptr, c->qkv_raw, s);
+        launch_gemm_generic<T>(Typed<T>::p(c->hbuf), 1, d.hidden, b, nullptr, n_qkv, EPI_STORE_F32, nullptr, c->qkv_raw, s);
         launch_rope_scatter<T>(c->qkv_raw, Typed<T>::p(w.bq), Typed<T>::p(w.bk), Typed<T>::p(w.bv), d_pos, 1,
                                d.n_q_heads, d.n_kv_heads, d.head_dim, c->rope_cos, c->rope_sin, Typed<T>::p(c->q),
                                Typed<T>::p(c->kc), Typed<T>::p(kl), Typed<T>::p(vl), s);

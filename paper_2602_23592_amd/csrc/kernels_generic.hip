@@ -269,24 +269,21 @@ void launch_gemm_generic(const T* A, int32_t M, int32_t K, const GemmB& B, const
 }
 
 // q (LDS) . k (one head of one cache row), summed in ascending order.  A lane reads its own row, so what bounds the
-// loop is the number of load instructions: fp32 heads of whole 16-byte vectors (the kernels that write the rows store
-// such vectors) are read four elements at a time.
+// loop is the number of load instructions: fp32 heads are read four elements at a time (head_dim is a multiple of 16).
 template <typename T>
 __device__ __forceinline__ float dot_head(const float* q, const T* __restrict__ k, int head_dim) {
   float dot = 0.f;
   if constexpr (sizeof(T) == 4) {
-    if (head_dim % 16 == 0) {
-      for (int d = 0; d < head_dim; d += 16) {
-        f32x4 v[4];
+    for (int d = 0; d < head_dim; d += 16) {
+      f32x4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(k + d + 4 * u);
+      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(k + d + 4 * u);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) dot += q[d + u] * v[u / 4][u % 4];
-      }
-      return dot;
+      for (int u = 0; u < 16; ++u) dot += q[d + u] * v[u / 4][u % 4];
     }
+  } else {
+    for (int d = 0; d < head_dim; ++d) dot += q[d] * ldf(k + d);
   }
-  for (int d = 0; d < head_dim; ++d) dot += q[d] * ldf(k + d);
   return dot;
 }
 
