@@ -132,10 +132,10 @@ typedef struct {
   float ms_realign[KEEP_REPORT_MAX_LAYERS];    /* re-align + concatenate kernel */
   float ms_prep[KEEP_REPORT_MAX_LAYERS];       /* row table, gather, first RMSNorm */
   float ms_qkv_gemm[KEEP_REPORT_MAX_LAYERS];   /* QKV projection GEMM alone */
-  float ms_rope[KEEP_REPORT_MAX_LAYERS];       /* bias + RoPE + scatter kernel */
+  float ms_rope[KEEP_REPORT_MAX_LAYERS];       /* bias + RoPE + scatter kernel (0 where the projection does it) */
   float ms_attn[KEEP_REPORT_MAX_LAYERS];       /* sparse-row attention kernel */
   float ms_oproj[KEEP_REPORT_MAX_LAYERS];      /* output projection GEMM (+ residual) */
-  float ms_norm2[KEEP_REPORT_MAX_LAYERS];      /* second RMSNorm */
+  float ms_norm2[KEEP_REPORT_MAX_LAYERS];      /* second RMSNorm (0 where the gate/up projection does it: one row) */
   float ms_gateup[KEEP_REPORT_MAX_LAYERS];     /* gate/up GEMM with fused SwiGLU */
   float ms_down[KEEP_REPORT_MAX_LAYERS];       /* down GEMM (+ residual) */
   float ms_score[KEEP_REPORT_MAX_LAYERS];      /* score reduction + selection, eval stream */
@@ -237,8 +237,8 @@ keep_status keep_select_groups(keep_ctx* ctx, const float* S, const int32_t* gro
 #define KEEP_STATIC_MAX_CANDIDATES 4096
 /* keep_select_groups for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It needs no context: the scratch that the selection uses
- * beyond its inputs and outputs (the candidates' lengths and their token total) lives in a device array built
- * into the library (32.5 KiB, held by every GPU the library runs on until the process ends), and the call
+ * beyond its inputs and outputs (the candidates' lengths, their token total, the row totals of S) lives in a device
+ * array built into the library (32.5 KiB, held by every GPU the library runs on until the process ends), and the call
  * makes no allocation, on the device or through any library.  Inputs and outputs are DEVICE memory:
  *   S:         DEVICE [(n_sel + 1) * n_sel], last row the query (as keep_select_groups, but on the device).
  *   groups:    DEVICE [n_sel], strictly ascending group ids below n_groups_total (not checked; ids are clamped

@@ -131,16 +131,18 @@ void launch_dequant_int4(const void* codes, const void* scale_zero, int32_t rows
 // lies past the end reads zeros and costs no memory traffic, which keeps the loop one straight line of loads with
 // exact wait counts, DEPTH steps ahead of their use, also across the ends of tiles.
 // With one row (decoding) the activations sit in LDS, and the RMSNorm in front of the projection is done there by
-// every workgroup for itself while its first weights are on their way: the row is 10 KB, and a kernel of its own
-// takes 4.6 us, the least any kernel takes here.
+// every workgroup for itself while its first weights are on their way: the row is 10 KB, and the launch that did it
+// took 4.6 us, as did the RoPE/scatter launch behind QKV and each launch that added K slices.
 // Per decoded token and layer at hidden 5120, FFN 13824 (550 MB of weights): 104 us = 5.3 TB/s, where K slices written
 // as partials and added by a second kernel, a norm and a RoPE/scatter kernel took 146 us; gate/up alone 49.0 us
-// (5.8 TB/s), vocabulary of 152064 rows 251 us (6.2 TB/s).
+// (5.8 TB/s), vocabulary of 152064 rows 251 us (6.2 TB/s).  With 16 rows every wave reads its activations from L2 beside
+// the weights: gate/up 55 us, output and down projection 25 us on average, QKV 21 us (64, 26 and 23 us where a cache of
+// 135 MB per layer is read and written in between).
 // ---------------------------------------------------------------------------------------------
 struct GemvArgs {
   const bf16_t* A;
   int M, K, N;            // N: output columns
-  int units;              // output columns (SwiGLU, RoPE: column pairs) per workgroup, at most 16 per tile
+  int units;              // output columns (SwiGLU, RoPE: column pairs) of a workgroup's tile, at most 16 per MFMA tile
   int tiles, red_offset;  // tiles of `units` in all; byte offset of the partial sums in LDS
   const bf16_t* norm_w;   // one row: RMSNorm weights to apply to A first, or NULL
   float eps;
@@ -174,8 +176,8 @@ __global__ void __launch_bounds__(GV_WAVES * 64, ONE_ROW ? 4 : 2) k_gemv(GemvArg
   constexpr int T = GV_WAVES * 64;
   constexpr int KS = W4 ? 128 : 64;                      // K per wave step
   constexpr int LD = W4 ? 1 : 2;                         // 16-byte loads per tile and step
-  // Steps requested ahead.  Two are enough (16 waves of a CU have 64 KB on their way), and more is slower: the gate/up
-  // launch at 27648 x 5120 takes 49.0 us with two, 50.1 with three, 51.7 with four.
+  // Steps requested ahead.  Two are enough (with bf16 weights 16 waves of a CU have NT x 64 KB on their way), and more is
+  // slower: the gate/up launch at 27648 x 5120 (NT = 2) takes 49.0 us with two, 50.1 with three, 51.7 with four.
   constexpr int DEPTH = W4 && NT == 1 ? 3 : 2;
   constexpr int MF = KS / 32;                            // MFMAs per tile and step
   constexpr int ADEPTH = ONE_ROW ? 1 : DEPTH;
@@ -475,7 +477,9 @@ static void launch_gemv_cfg(GemvArgs g, hipStream_t s) {
   // size, over 512 persistent workgroups (256 where half as many rows would leave the tiles mostly empty): at
   // 5120 rows of output, K = 5120 and 13824, 19.1 us on average against 25.6 us with tiles of 16 rows.  With several
   // activation rows every workgroup reads them all from L2, so there are 256 workgroups of twice the tiles
-  // (16 rows, same shapes: 26.1 us against 32.8).
+  // (16 rows, same shapes: 26.1 us against 32.8).  QKV is not dealt out: its tiles are 8 or 16 column pairs, one per
+  // workgroup, so that none straddles q, k, v or a head.  7168 rows, K = 5120: 224 workgroups of 16 pairs, 16.9 us with
+  // one row (4.3 TB/s).
   const int total = EPI == EPI_QKV_ROPE ? g.N / 2 : g.N;
   const int slots = ONE_ROW && (total + 511) / 512 > CAP / 2 ? 512 : 256;
   const int rounds = (total + slots * CAP - 1) / (slots * CAP);
@@ -669,9 +673,16 @@ bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
       if (B.n_rows[p] % SK_BN) return false;
     if (epilogue == EPI_SWIGLU_STORE && N % SK_BN) return false;
   }
-  // Where streaming the weights once stops paying (measured on unit caching at the 14B shape, 48 layers): with
-  // bf16 weights the matrix-core tiles are faster from 17 rows on; the 4-bit form moves a quarter of the bytes and
-  // wins up to 48 rows (33 rows: 7.3 ms against 8.4 ms, 48: 8.5 against 8.6, 64: 9.5 against 8.8).
+  // Where streaming the weights stops paying, in us per layer of a unit cached on its own, all launches of a layer, at the
+  // 7B / 14B / 32B shapes.  k_gemv holds up to 16 rows in one MFMA tile and is no slower than what takes over at 17:
+  //   bf16, k_gemv against the matrix-core tiles: 2 rows 124 / 137 / 207 against 147 / 160 / 260, 8 rows 130 / 137 / 209
+  //   against 149 / 157 / 252, 16 rows 143 / 150 / 231 against 150 / 158 / 253.  Launch by launch with 16 rows at the 14B
+  //   shape: gate/up 54.9 against 57.6 + 4.7 (the pass that adds the cuts along K), output and down projection 25.0 against
+  //   21.7 + 4.4 on average, QKV 20.7 against 17.3 + 4.7.
+  //   4-bit, k_gemv against k_gemm_skinny_w4: 2 rows 78 / 81 / 113 against 86 / 96 / 120, 8 rows 81 / 84 / 116 against
+  //   90 / 99 / 125, 16 rows 93 / 94 / 133 against 96 / 101 / 133.
+  // k_gemm_skinny_w4 moves a quarter of the tiles' bytes and wins up to 48 rows (14B shape, 48 layers: 33 rows 6.9 ms
+  // against 7.8 with bf16 weights, 48 rows 8.1 against 8.2).
   if (gemv_fits(M, K, B)) return true;
   return B.has_w4 && M > GV_MAX_ROWS && M <= 48 && epilogue != EPI_QKV_ROPE && (size_t)M * (size_t)ld <= SK_MAX_PART_FLOATS;
 }

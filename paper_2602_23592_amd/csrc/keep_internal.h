@@ -83,7 +83,7 @@ enum GemmEpilogue {
   EPI_RESIDUAL_STORE = 1, // C (T) = residual (T) + acc
   EPI_SWIGLU_STORE = 2,   // C (T) = silu(acc_gate) * acc_up   (B = gate rows, B2 = up rows)
   EPI_QKV_ROPE = 3,       // fused QKV projection: bias, RoPE at the row's position, q / compact k written, K and V
-                          // scattered into the cache rows (matrix-core path, 256 x 256 tiles, head_dim 128)
+                          // scattered into the cache rows (bf16 matrix-core family, head_dim 128)
 };
 
 // Where the fused QKV epilogue reads positions and writes its results (device pointers).
@@ -187,17 +187,17 @@ void launch_score_finish(const float* rowmass, const int32_t* d_row_start, int32
                          hipStream_t s);
 
 // MFMA (bf16, head_dim 128) kernels
-// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernel for launches of at
-// most 48 rows, and of the tiles that are cut along K to fill the last round of workgroups.  NULL: neither.
+// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernel for 17 to 48 rows on the 4-bit
+// form, and of the tiles that are cut along K to fill the last round of workgroups.  NULL: no weight streaming, no cuts.
 size_t gemm_ws_bytes();
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws = nullptr,
                       const QkvEpilogue* qkv = nullptr, const RowNorm* norm = nullptr);
-// true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows, weight-streaming kernel)
+// true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows that k_gemv holds in LDS)
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
-// true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows
-// (weight-streaming kernel) and launches on tiles with 128 columns per wave (one head), which are all where each part's
-// width is a multiple of 128; elsewhere the caller projects to fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel.
+// true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows (k_gemv) and
+// every launch on tiles.  That leaves 17 to 48 rows on the 4-bit form (k_gemm_skinny_w4), where the caller projects to
+// fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel, as it does for the token-granularity scheme.
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // bf16 expansion of an INT4 matrix: out[rows, K] = bf16((code - zero) * scale)
 void launch_dequant_int4(const void* codes, const void* scale_zero, int32_t rows, int32_t K, void* out, hipStream_t s);

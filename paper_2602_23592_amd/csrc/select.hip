@@ -18,8 +18,10 @@ constexpr int SEL_THREADS = 1024;
 //
 // A workgroup owns 16 rows.  Waves 1..4 fetch the next 256 columns into LDS (consecutive threads on consecutive
 // columns) while 16 lanes of wave 0 add the present ones, so the kernel costs the chain of m dependent additions and
-// no memory latency beyond the first block's: 8 us at 1024 candidates.  The last workgroup instead forms the candidates' lengths and their
-// total for callers that pass the memories' indices (`prep`).
+// no memory latency beyond the first block's: 8 us at 1024 candidates on an idle chip (beside a product that fills the
+// chip it waits for workgroups of that one to end).  It sums every row, also those a selection never reads; where scores
+// are formed row by row some were not formed yet, and their totals mean nothing until a later launch.  The last workgroup
+// instead forms the candidates' lengths and their total for callers that pass the memories' indices (`prep`).
 // ---------------------------------------------------------------------------------------------
 constexpr int RT_ROWS = 16, RT_COLS = 256, RT_LD = RT_COLS + 4;
 constexpr int RT_THREADS = 64 + RT_COLS;
