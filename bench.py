@@ -505,7 +505,7 @@ def extras(a, torch, ks, kb, main_case, main_ratios, sched):
 
 
 def sweep(a, torch, ks, kb):
-    """BASELINE's stress sweep: recompute ratio 5/10/20/30 % x hops 1-4 on one prompt (default: the 65 536-token,
+    """The stress sweep: recompute ratio 5/10/20/30 % x hops 1-4 on one prompt (default: the 65 536-token,
     1 024-memory one).  One JSON line per point."""
     c = Case(a.workload, a, torch, ks, kb)
     c.make_prompt()

@@ -61,7 +61,7 @@ def stats(argv):
     bench = json.loads([l for l in open(benchlog) if l.startswith("{")][-1])
     with open(out, "w") as o:
         o.write("# rocprofv3 kernel stats: keep_prefill, %s (one MI355X)\n\n" % bench["config"]["workload"].split(":")[0])
-        o.write("Command (from /tmp with TMPDIR=/tmp on the GPU box):\n\n    %s\n\n" % cmd)
+        o.write("Command (from /tmp with TMPDIR=/tmp):\n\n    %s\n\n" % cmd)
         o.write("bench.py pauses the profiler during set-up (roctxProfilerPause/Resume, honoured with --marker-trace), so "
                 "the rows cover the warm-up, the timed steps and the one fully instrumented step.\n\n")
         o.write("| kernel | calls | total ms | avg us | % | min us | max us |\n|---|---|---|---|---|---|---|\n")
@@ -111,7 +111,7 @@ def traffic(argv):
         o.write("\n")
     with open(out_md, "w") as o:
         o.write("# rocprofv3 counters FETCH_SIZE / WRITE_SIZE: keep_prefill, workload qwen14b_32k (one MI355X)\n\n")
-        o.write("Commands (each from /tmp with TMPDIR=/tmp on the GPU box, one counter per run):\n\n    %s\n    %s\n\n"
+        o.write("Commands (each from /tmp with TMPDIR=/tmp, one counter per run):\n\n    %s\n    %s\n\n"
                 % (cmd.replace("COUNTER", "FETCH_SIZE"), cmd.replace("COUNTER", "WRITE_SIZE")))
         o.write("Calibration (same runs): the %d KiB device-to-device copy reads %.0f KiB by FETCH_SIZE and writes %.0f KiB "
                 "by WRITE_SIZE, so true bytes = %.2f x FETCH_SIZE and %.2f x WRITE_SIZE.  The counters sit between L2 and "
@@ -138,7 +138,7 @@ def counters(argv):
     dirs = argv[3:]
     want = [w for w in part.split(",") if w and w != "-"]
     with open(out_md, "w") as o:
-        o.write("# rocprofv3 --pmc counters per kernel (one MI355X)\n\nCommand (from /tmp with TMPDIR=/tmp on the GPU box; "
+        o.write("# rocprofv3 --pmc counters per kernel (one MI355X)\n\nCommand (from /tmp with TMPDIR=/tmp; "
                 "one run per counter set, COUNTERS = the names listed under each kernel):\n\n    %s\n\nValues are sums over all "
                 "dispatches of the kernel in the run and over the chip's counter instances (SQ counters: all CUs).\n\n" % cmd)
         merged = collections.defaultdict(dict)

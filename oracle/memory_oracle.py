@@ -4,7 +4,7 @@ TEST INFRASTRUCTURE ONLY: tests, the smoke check and the bench's CPU leg may use
 product path never does.  Plain Python, written from the paper's description:
 
   * memories are clustered into groups of segments (the clustering itself, a sentence
-    encoder, is outside this build: callers say which group a segment belongs to);
+    encoder, is outside this library: callers say which group a segment belongs to);
   * a group is STATIC when none of its segments changed during the recent `t` steps, else
     DYNAMIC; a new group starts dynamic;
   * the KV cache of a static group is computed once for the whole group (segments
