@@ -684,7 +684,7 @@ def main():
     default_run = (a.workload == "qwen14b_32k" and a.schedule is None and a.ratio is None and a.budget is None
                    and not a.random_cache and a.sparse_rows == 0 and not tokens_mode)
     traffic, traffic_src = stored_traffic() if default_run else (None, "not the workload of the stored counter run")
-    roofline = {"kernel": "k_gemm_mfma<256,256,...,SWIGLU> + k_gemm_fixup (gate/up projection with fused SiLU*mul; "
+    roofline = {"kernel": "k_gemm_256<SWIGLU> + k_gemm_fixup (gate/up projection with fused SiLU*mul; "
                           "256x256 tiles, the last partly filled round cut along K)",
                 "bound": "mfma", "achieved": gu["achieved"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": gu["frac"], "traffic": traffic, "traffic_source": traffic_src,

@@ -101,8 +101,8 @@ def traffic(argv):
             copy_kib = int(part) * 1024
     f_scale = copy_kib / calib["FETCH_SIZE"] if calib["FETCH_SIZE"] else 0.0
     w_scale = copy_kib / calib["WRITE_SIZE"] if calib["WRITE_SIZE"] else 0.0
-    gu = lambda c: sum(v[1] for k, v in pk[c].items() if k.startswith("k_gemm_mfma<256, 256, 4, 2, 2") or k.startswith("k_gemm_fixup<256, 256, 4, 2, 2"))
-    launches = sum(v[0] for k, v in pk["FETCH_SIZE"].items() if k.startswith("k_gemm_mfma<256, 256, 4, 2, 2"))
+    gu = lambda c: sum(v[1] for k, v in pk[c].items() if k.startswith("k_gemm_256<2") or k.startswith("k_gemm_fixup<256, 256, 2, 2, 2"))
+    launches = sum(v[0] for k, v in pk["FETCH_SIZE"].items() if k.startswith("k_gemm_256<2"))
     bytes_per_launch = (gu("FETCH_SIZE") * f_scale + gu("WRITE_SIZE") * w_scale) * 1024.0 / max(1, launches)
     with open(out_json, "w") as o:
         json.dump({"bytes_per_launch": int(bytes_per_launch), "launches": launches, "fetch_scale": round(f_scale, 4),
@@ -117,7 +117,7 @@ def traffic(argv):
                 "by WRITE_SIZE, so true bytes = %.2f x FETCH_SIZE and %.2f x WRITE_SIZE.  The counters sit between L2 and "
                 "the fabric: they count L2 misses, whether the Infinity Cache or HBM serves them.\n\n"
                 % (copy_kib, calib["FETCH_SIZE"], calib["WRITE_SIZE"], f_scale, w_scale))
-        o.write("Gate/up GEMM (k_gemm_mfma<256,256,4,2,SWIGLU> + its fix-up): %d launches, %.3f GB per launch (scaled).\n\n"
+        o.write("Gate/up GEMM (k_gemm_256<SWIGLU> + its fix-up): %d launches, %.3f GB per launch (scaled).\n\n"
                 % (launches, bytes_per_launch / 1e9))
         att = [pk[c].get("k_attn_mfma", (0, 0.0, 0.0)) for c in ("FETCH_SIZE", "WRITE_SIZE")]
         if att[0][0]:

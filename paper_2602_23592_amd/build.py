@@ -3,6 +3,7 @@
     python -m paper_2602_23592_amd.build
 """
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -22,6 +23,28 @@ FLAGS = [
 ]
 
 
+# Kernels whose accumulators are written by inline assembly: a spill of one right behind a product would store a stale
+# value, so these must not use scratch memory at all.
+NO_SCRATCH = {"gemm_mfma.hip": "k_gemm_256"}
+
+
+def check_scratch(src, report):
+    if src not in NO_SCRATCH:
+        return
+    kernel, seen = None, 0
+    for line in report.splitlines():
+        name = re.search(r"Function Name: (\S+)", line)
+        if name:
+            kernel = name.group(1)
+        size = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+        if size and kernel and NO_SCRATCH[src] in kernel:
+            seen += 1
+            if int(size.group(1)):
+                raise RuntimeError("%s uses %s bytes of scratch memory per lane; it must use none" % (kernel, size.group(1)))
+    if not seen:
+        raise RuntimeError("no resource report for %s in %s" % (NO_SCRATCH[src], src))
+
+
 def sources():
     return sorted(f for f in os.listdir(CSRC) if f.endswith(".hip"))
 
@@ -32,12 +55,15 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
 
     def compile_one(src):
         obj = os.path.join(OBJ, src[:-4] + ".o")
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        report = ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"] if src in NO_SCRATCH else []
+        cmd = [HIPCC, *FLAGS, *report, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))
+        check_scratch(src, r.stderr)
         if verbose:
-            errs = [l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l and l.strip()]
+            errs = [l for l in r.stderr.splitlines()
+                    if "packed-fp32-ops" not in l and "kernel-resource-usage" not in l and l.strip()]
             print("compiled", src, ("\n" + "\n".join(errs)) if errs else "", flush=True)
         return obj
 

@@ -17,6 +17,7 @@
 // gate[m, n] and up[m, n] in matching accumulator registers, and the fused QKV epilogue (bias, RoPE,
 // compact q / k rows, scatter of K and V into the cache).
 #include <algorithm>
+#include <type_traits>
 
 #include "keep_internal.h"
 
@@ -418,6 +419,463 @@ __global__ void __launch_bounds__(WM* WN * 64)
 #undef GEMM_STAGE
 #undef QKV_STAGE_TABLES
 
+// ---------------------------------------------------------------------------------------------
+// k_gemm_256: 256x256 tiles, four waves of 128x128, one per SIMD.
+//
+// Bound by the matrix cores and by what feeds them: LDS reads (64 KB x 2 per 64-deep slice here; eight waves of 64x128
+// read 192 KB), the global -> LDS loads, and the clock, which falls with the power they all draw.  With one wave per SIMD
+// nothing but this wave's own instruction order hides latency, so the order is written down: the accumulators sit in the
+// accumulation registers (inline assembly: the compiler otherwise copies them to and fro around every product), and each
+// k-step of 64 MFMAs carries the 16 operand reads of the next one, two thirds of an MFMA slot apart or more.  The reads of
+// a slice's second k-step are done halfway through its first (`X`: every wave has read the stage), so the slice after the
+// next is requested from there on, spread evenly, one load in five MFMAs (two in five and more at once stall the wave in
+// front of the address unit), and has a slice and a half to arrive (`Y`).
+//
+// (Inline assembly hides the products from the compiler's hazard checks.  Nothing but products may therefore touch an
+// accumulator before the wait behind the last one: the accumulators are read by get(), in assembly too, and the build
+// refuses a k_gemm_256 with scratch memory, where one might have been spilled right behind its product.)
+//
+// The weights are the A operand and the activations the B operand, and the weight rows of two neighbouring 16-row tiles
+// are dealt out alternately by fours: a lane then holds eight consecutive output columns of one row, and the epilogues
+// read and write 16 bytes a lane (2 bytes before: 256 stores per wave and as many loads of the residual).
+//
+// A wave's rows are 64 consecutive ones of either half of the tile, so that in a last tile with at most 128 rows of
+// the launch every wave has half its rows and does half its products (MI = 4), or none (MI = 0: loads and barriers only).
+//
+// Standalone, same card, alternating with eight waves of 64x128 in the order the compiler gave (rows x K x columns, us):
+//   gate/up 3328 x 5120 x 27648: 716 against 768 (1.32 PFLOP/s); down 3328 x 13824 x 5120: 350 against 385; O 5120 x 5120 x
+//   5120: 216 against 244; QKV 5120 x 5120 x 7168: 296 against 315.  (An approximate reciprocal in SwiGLU: gate/up 703; not
+//   kept, its last bit reaches every later layer.)  The loads packed behind
+//   one barrier instead (two in eight products): gate/up 8192 rows 7 % slower; the loop on the compiler's own register
+//   assignment: 60 % slower (accumulators copied).
+// ---------------------------------------------------------------------------------------------
+constexpr int G2_THREADS = 256;
+constexpr int G2_STAGE = 512 * 64;  // elements of an LDS stage: 256 activation rows, then 256 weight rows
+
+// swizzle of the weight rows' 16-byte chunks: a fragment's 16 lanes read rows 0-3, 8-11, 16-19 and 24-27 of a block of 32
+__device__ __forceinline__ int g2_wswz(int row) { return ((row >> 1) & 1) | (((row >> 3) & 3) << 1); }
+
+struct G2Src {  // where the wave's share of a slice comes from
+  const bf16_t *a, *b;
+  uint32_t a_bytes, b_bytes;
+  uint32_t a_off[8], b_off[8];
+};
+
+typedef void __attribute__((address_space(3))) * g2_lptr_t;
+
+#define G2_FENCE __builtin_amdgcn_sched_barrier(0)
+#define G2_BARRIER                   \
+  {                                  \
+    G2_FENCE;                        \
+    __builtin_amdgcn_s_barrier();    \
+    G2_FENCE;                        \
+    asm volatile("" ::: "memory");   \
+  }
+
+// load r of 16 of slice `s` into stage `st`: even ones activations, odd ones weights, 8 rows each
+__device__ __forceinline__ void g2_load(const G2Src& src, uint16_t* smem, int wave, int s, int st, int r) {
+  const int i = r >> 1;
+  uint16_t* dst = smem + st * G2_STAGE + (r & 1) * (G2_STAGE / 2) + (wave * 8 + i) * 512;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(r & 1 ? src.b : src.a), 0,
+                                                      r & 1 ? src.b_bytes : src.a_bytes, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (g2_lptr_t)dst, 16, r & 1 ? src.b_off[i] : src.a_off[i], s * 128, 0, 0);
+}
+
+// One slice.  Behind X either slice kt + 2 is requested (NEXT), or, in the last two slices of a tile, what its epilogue
+// will read (tail(r), r = 0 .. 15, with `tails`): the stage is free by then and the loads' time is hidden.
+enum G2Slice { G2_NEXT, G2_LAST_BUT_ONE, G2_LAST };
+
+template <int MI, G2Slice KIND, typename Tail>
+__device__ __forceinline__ void g2_slice(f32x4 (&acc)[8][8], bf16x8 (&wf)[2][8], bf16x8 (&xf)[2][8], const G2Src& src,
+                                         uint16_t* smem, int wave, const int (&x_off)[2], const int (&w_off)[2], int kt,
+                                         bool tails, const Tail& tail) {
+  constexpr int NM = MI ? MI * 8 : 32;          // products per k-step
+  constexpr int NR = MI ? MI + 8 : 0;           // operand reads per k-step
+  constexpr int X = MI == 8 ? 34 : 22;          // all reads of the second k-step lie in front (every 1.75 products)
+  constexpr int DS2 = MI == 8 ? 10 : 5;         // half products between loads
+  constexpr int BEHIND_X = (2 * (NM - 2 - X)) / DS2 + 1;  // loads between X and the end of the first k-step
+  const int st = kt & 1;
+  auto read = [&](int p, int ks, int stage, int r) {
+    const uint16_t* base = smem + stage * G2_STAGE;
+    if (r < 8)
+      wf[p][r] = *reinterpret_cast<const bf16x8*>(base + G2_STAGE / 2 + w_off[ks] + (r >> 1) * 32 * 64 + (r & 1) * 4 * 64);
+    else
+      xf[p][r - 8] = *reinterpret_cast<const bf16x8*>(base + x_off[ks] + ((r - 8) >> 2) * 128 * 64 + ((r - 8) & 3) * 16 * 64);
+  };
+#pragma clang loop unroll(full)
+  for (int half = 0; half < 2; ++half) {
+#pragma clang loop unroll(full)
+    for (int n = 0; n < NM; ++n) {
+      if (MI)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                     : "+a"(acc[n >> 3][n & 7])
+                     : "v"(wf[half][n & 7]), "v"(xf[half][n >> 3]));
+      if (half == 0 || KIND != G2_LAST) {
+#pragma clang loop unroll(full)
+        for (int r = 0; r < NR; ++r)
+          if (n == (half ? r * (NM * 3 / 4) / (NR ? NR : 1) : r * 7 / 4)) {
+            G2_FENCE;
+            read(half ^ 1, half ^ 1, half ? st ^ 1 : st, r);
+            G2_FENCE;
+          }
+      }
+      if (half == 0 && n == X) {  // X: this wave's reads of the stage are back, and with the barrier every wave's
+        G2_FENCE;
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        G2_BARRIER
+      }
+#pragma clang loop unroll(full)
+      for (int r = 0; r < 16; ++r)
+        if (n + half * NM == X + 1 + r * DS2 / 2) {
+          G2_FENCE;
+          if (KIND == G2_NEXT)
+            g2_load(src, smem, wave, kt + 2, st, r);
+          else if (tails)
+            tail(smem + st * G2_STAGE, KIND == G2_LAST, r);
+          G2_FENCE;
+        }
+    }
+    if (half == 0 && KIND != G2_LAST) {  // Y: slice kt + 1 has landed
+      G2_FENCE;
+      if (KIND == G2_NEXT || tails)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(BEHIND_X));
+      else
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      G2_BARRIER
+    }
+  }
+  G2_FENCE;
+}
+
+// The slices kt0 .. kt1 - 1 of a tile, at least two; the first two are on their way (16 loads of this wave each).
+template <int MI, typename Tail>
+__device__ __forceinline__ void g2_loop(f32x4 (&acc)[8][8], const G2Src& src, uint16_t* smem, int wave, int lane, int wm,
+                                        int wn, int kt0, int kt1, bool tails, const Tail& tail) {
+  bf16x8 wf[2][8], xf[2][8];
+  int x_off[2], w_off[2];
+  {
+    const int l = lane & 15, c = lane >> 4;
+    const int wr = 8 * (l >> 2) + (l & 3);  // weight row inside a block of 32 (its tile's other half: + 4)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      x_off[ks] = lds_off<64>(wm * 64 + l, ks * 4 + c);
+      w_off[ks] = (wn * 128 + wr) * 64 + (((ks * 4 + c) ^ g2_wswz(wr)) << 3);
+    }
+  }
+  {  // zeros (while the first slices are on their way), as products: what the compiler cannot rebuild it does not copy
+    u32x4 zero = {0, 0, 0, 0};
+    asm volatile("s_nop 4" : "+v"(zero));
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(acc[i][j]) : "v"(zero));
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));  // slice kt0 has landed
+  G2_BARRIER
+  if (MI) {
+    const uint16_t* base = smem + (kt0 & 1) * G2_STAGE;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      wf[0][j] = *reinterpret_cast<const bf16x8*>(base + G2_STAGE / 2 + w_off[0] + (j >> 1) * 32 * 64 + (j & 1) * 4 * 64);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+      xf[0][i] = *reinterpret_cast<const bf16x8*>(base + x_off[0] + (i >> 2) * 128 * 64 + (i & 3) * 16 * 64);
+  }
+  int kt = kt0;
+  for (; kt + 2 < kt1; ++kt) g2_slice<MI, G2_NEXT>(acc, wf, xf, src, smem, wave, x_off, w_off, kt, tails, tail);
+  g2_slice<MI, G2_LAST_BUT_ONE>(acc, wf, xf, src, smem, wave, x_off, w_off, kt, tails, tail);
+  g2_slice<MI, G2_LAST>(acc, wf, xf, src, smem, wave, x_off, w_off, kt + 1, tails, tail);
+  asm volatile("s_nop 15\n s_nop 15" ::: "memory");  // the last products are in the accumulators
+  G2_FENCE;
+}
+
+// eight consecutive values of a row: accumulator tiles 2 jj and 2 jj + 1
+__device__ __forceinline__ uint4 g2_pack(const float (&v)[8]) {
+  return make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+}
+__device__ __forceinline__ void g2_unpack(const uint4& u, float (&v)[8]) {
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[2 * i] = __uint_as_float(w[i] << 16);
+    v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(G2_THREADS, 1)
+    k_gemm_256(const bf16_t* __restrict__ A, int M, int K, MfmaB B, const bf16_t* __restrict__ B2, int N,
+               const bf16_t* __restrict__ residual, void* __restrict__ Cv, int tiles_m, int tiles_n, int full_per_xcd,
+               int split_s, float* __restrict__ part, QkvEpilogue qe) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  // workgroup -> tile: as in k_gemm_mfma
+  const int n_tiles = tiles_m * tiles_n;
+  const int per_xcd = (n_tiles + 7) >> 3;
+  const int xcd = (int)(blockIdx.x & 7), j_x = (int)(blockIdx.x >> 3);
+  int tl = j_x, piece = 0, pieces = 1;
+  if (j_x >= full_per_xcd) {
+    tl = full_per_xcd + (j_x - full_per_xcd) / split_s;
+    piece = (j_x - full_per_xcd) % split_s;
+    pieces = split_s;
+  }
+  const int t = xcd * per_xcd + tl;
+  if (tl >= per_xcd || t >= n_tiles) return;
+  int tile_m, tile_n;
+  gemm_tile_of<256>(t, tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * 256, n0 = tile_n * 256;  // n0 in rows of the weight tile (SwiGLU: 128 output columns)
+
+  // ---- the wave's 64 rows of either operand, 8 per load: lane l's 16 bytes land at (LDS base) + 16 l, so the lane whose
+  // bytes land in chunk pc of a row fetches the chunk that the swizzle keeps there
+  G2Src src;
+  {
+    src.a = A + (size_t)m0 * K;
+    src.a_bytes = (uint32_t)min(256, M - m0) * K * 2;
+    int first = wave * 64;  // first weight row of the wave's share inside src.b
+    if (EPI == EPI_SWIGLU_STORE) {  // waves 0, 2: gate rows, 1, 3: up rows, of column block wave / 2
+      src.b = (wave & 1 ? B2 : B.ptr[0]) + (size_t)(n0 / 2) * K;
+      first = (wave >> 1) * 64;
+    } else {  // (a tile lies in one part: their widths are multiples of 256)
+      const bf16_t* base = B.ptr[0];
+      int begin = 0;
+      if (B.n_parts > 1 && n0 >= B.begin[1]) base = B.ptr[1], begin = B.begin[1];
+      if (B.n_parts > 2 && n0 >= B.begin[2]) base = B.ptr[2], begin = B.begin[2];
+      src.b = base + (size_t)(n0 - begin) * K;
+    }
+    src.b_bytes = (uint32_t)(EPI == EPI_SWIGLU_STORE ? 128 : 256) * K * 2;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = i * 8 + lane / 8, pc = lane & 7;
+      src.a_off[i] = (uint32_t)min(wave * 64 + r, M - 1 - m0) * K * 2 + (pc ^ ((r >> 1) & 7)) * 16;
+      src.b_off[i] = (uint32_t)(first + r) * K * 2 + (pc ^ g2_wswz(r)) * 16;
+    }
+  }
+  const int kt0 = (int)((long)piece * (K / 64) / pieces), kt1 = (int)((long)(piece + 1) * (K / 64) / pieces);
+
+  const int c8 = 8 * (lane >> 4);  // the lane's output columns: c8 + 32 jj + 0..7 of the wave's 128
+  auto rt = [&](int i) { return (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + (lane & 15); };  // its row of tile i
+
+  // ---- what the epilogue reads comes to LDS during the last two slices, the first half of the tile's rows in the first
+  // one.  Residual: the 16 bytes of tile i, column block jj land where the lane that fetched them reads them back.
+  // Fused QKV: cos / sin rows, picked by each row's rotation position: 32 chunks of 16 bytes (cos, then sin), chunk c
+  // kept at c ^ (row % 16); a load fills two rows.  The rows' cache positions sit behind the stages.  (Tiles that hold
+  // only value columns need no table.)  Pieces of a tile have no epilogue.
+  const bool qkv_table = EPI == EPI_QKV_ROPE && n0 < qe.q_dim + qe.kv_dim;
+  const bool tails = pieces == 1 && (EPI == EPI_RESIDUAL_STORE || qkv_table);
+  int32_t* spos = reinterpret_cast<int32_t*>(smem + 2 * G2_STAGE);
+  int rot = 0;  // rotation position of tile row (lane / 32) * 128 + wave * 32 + lane % 32
+  if (EPI == EPI_QKV_ROPE && pieces == 1) {
+    const int r = (lane >> 5) * 128 + wave * 32 + (lane & 31), gm = min(m0 + r, M - 1);
+    const int p = qe.row_pos[gm];
+    spos[r] = p;
+    rot = p - (qe.row_lo ? qe.row_lo[gm] : 0);
+  }
+  const auto res_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(EPI == EPI_RESIDUAL_STORE ? residual + (size_t)m0 * N + n0 : nullptr), 0,
+      (uint32_t)((min(256, M - m0) - 1) * N + min(256, N - n0)) * 2, 0x00020000);
+  auto tail = [&](uint16_t* stage, int half, int r) {
+    if (EPI == EPI_RESIDUAL_STORE) {
+      const int row = min(rt(half * 4 + (r >> 2)), M - 1 - m0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(res_rsrc, (g2_lptr_t)(stage + (wave * 16 + r) * 512), 16,
+                                               (uint32_t)(row * N + wn * 128 + c8 + 32 * (r & 3)) * 2, 0, 0, 0);
+    } else if (EPI == EPI_QKV_ROPE) {
+      const int even = __builtin_amdgcn_readlane(rot, half * 32 + 2 * r), odd = __builtin_amdgcn_readlane(rot, half * 32 + 2 * r + 1);
+      const int ch = (lane & 31) ^ ((2 * r + (lane >> 5)) & 15);
+      const float* s = (ch < 16 ? qe.rope_cos : qe.rope_sin) + (size_t)(lane < 32 ? even : odd) * 64 + (ch & 15) * 4;
+      __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)s,
+                                       (g2_lptr_t)(stage + (wave * 32 + 2 * r) * 256), 16, 0, 0);
+    }
+  };
+
+#pragma unroll
+  for (int r = 0; r < 16; ++r) g2_load(src, smem, wave, kt0, kt0 & 1, r);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) g2_load(src, smem, wave, kt0 + 1, (kt0 & 1) ^ 1, r);
+  G2_FENCE;
+
+  auto tile = [&](auto mi) {
+    constexpr int MI = decltype(mi)::value;
+    f32x4 acc[8][8];  // [activation tile][weight tile]
+    g2_loop<MI>(acc, src, smem, wave, lane, wm, wn, kt0, kt1, tails, tail);
+    // (the lane's number anew: what the epilogue derives from it is not to be kept in registers through the loop)
+    int el = lane;
+    asm volatile("" : "+v"(el));
+    const int ec8 = 8 * (el >> 4), erow = wm * 64 + (el & 15);
+    // Rows past M were computed from row M - 1, as was everything they need: they are stored to that row, the same
+    // bytes again.  That keeps the epilogue free of branches, around which the compiler would keep all the accumulators
+    // in vector registers at once; the fences have it take them a row at a time.
+    auto row_of = [&](int i) { return min((i >> 2) * 128 + (i & 3) * 16 + erow, M - 1 - m0); };
+    // (read out of the accumulation registers here: the compiler would do it for all of them behind the last product)
+    auto get = [&](int i, int jj, float (&v)[8]) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][2 * jj + (e >> 2)][e & 3]));
+    };
+    if (pieces > 1) {  // partial tile [256][256] in tile coordinates
+      const int rem_per_xcd = per_xcd - full_per_xcd;
+      float* pt = part + ((size_t)(xcd * rem_per_xcd + (tl - full_per_xcd)) * split_s + piece) * (256 * 256);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        G2_FENCE;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          float v[8];
+          get(i, jj, v);
+          float* dst = pt + row_of(i) * 256 + wn * 128 + 32 * jj + ec8;
+          *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+          *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        }
+      }
+      return;
+    }
+    if constexpr (EPI == EPI_QKV_ROPE) {
+      // The wave's 128 columns are one head: query head, key head or value head by where they start.  RoPE pairs
+      // column c with c + 64: jj and jj + 2, same lane, same register.
+      const int col0 = n0 + wn * 128;
+      const int kind = col0 < qe.q_dim ? 0 : (col0 < qe.q_dim + qe.kv_dim ? 1 : 2);
+      const int hcol = kind == 0 ? col0 : (kind == 1 ? col0 - qe.q_dim : col0 - qe.q_dim - qe.kv_dim);  // column inside q / k / v
+      const bf16_t* bias = reinterpret_cast<const bf16_t*>(qe.bias[kind]);
+      float bv[4][8] = {};
+      if (bias && MI) {
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) bv[jj][e] = bf16_bits_to_f32(bias[hcol + 32 * jj + ec8 + e].bits);
+      }
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __syncthreads();  // the tables are there
+      auto v_rows = [&]() {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          G2_FENCE;
+          bf16_t* dst = reinterpret_cast<bf16_t*>(qe.v_cache) + (size_t)spos[row_of(i)] * qe.kv_dim + hcol + ec8;
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) {
+            float v[8];
+            get(i, jj, v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += bv[jj][e];
+            *reinterpret_cast<uint4*>(dst + 32 * jj) = g2_pack(v);
+          }
+        }
+      };
+      auto qk_rows = [&](auto is_key) {
+        constexpr bool KEY = decltype(is_key)::value;
+        bf16_t* out = reinterpret_cast<bf16_t*>(KEY ? qe.k_compact : qe.q) + hcol + ec8;
+        const int ld = KEY ? qe.kv_dim : qe.q_dim;
+        // cos / sin of row i: [cos, sin][column block][half of the lane's eight columns]; read a row ahead
+        f32x4 tab[2][2][2][2];
+        int pos[2] = {0, 0};
+        auto read_table = [&](int i) {
+          const int row = row_of(i);
+          const float* t = reinterpret_cast<const float*>(smem + ((kt1 + (i >> 2)) & 1) * G2_STAGE) + (row & 127) * 128;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const int ch = 16 * (k >> 2) + 8 * ((k >> 1) & 1) + (ec8 >> 2) + (k & 1);
+            tab[i & 1][k >> 2][(k >> 1) & 1][k & 1] = *reinterpret_cast<const f32x4*>(t + ((ch ^ (row & 15)) << 2));
+          }
+          if (KEY) pos[i & 1] = spos[row];
+        };
+        if (MI) read_table(0);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          G2_FENCE;
+          if (i + 1 < MI) read_table(i + 1);
+          G2_FENCE;
+          bf16_t* d1 = out + (size_t)(m0 + row_of(i)) * ld;
+          bf16_t* d2 = reinterpret_cast<bf16_t*>(qe.k_cache) + (size_t)pos[i & 1] * qe.kv_dim + hcol + ec8;
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            float lo[8], hi[8], ol[8], oh[8];
+            get(i, jj, lo);
+            get(i, jj + 2, hi);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              lo[e] += bv[jj][e];
+              hi[e] += bv[jj + 2][e];
+              const float cs = tab[i & 1][0][jj][e >> 2][e & 3], sn = tab[i & 1][1][jj][e >> 2][e & 3];
+              ol[e] = lo[e] * cs - hi[e] * sn;
+              oh[e] = hi[e] * cs + lo[e] * sn;
+            }
+            const uint4 pl = g2_pack(ol), ph = g2_pack(oh);
+            *reinterpret_cast<uint4*>(d1 + 32 * jj) = pl;
+            *reinterpret_cast<uint4*>(d1 + 32 * jj + 64) = ph;
+            if (KEY) {
+              *reinterpret_cast<uint4*>(d2 + 32 * jj) = pl;
+              *reinterpret_cast<uint4*>(d2 + 32 * jj + 64) = ph;
+            }
+          }
+        }
+      };
+      if (kind == 2)
+        v_rows();
+      else if (kind == 1)
+        qk_rows(std::true_type{});
+      else
+        qk_rows(std::false_type{});
+      return;
+    }
+    uint4 res[2][4];
+    auto read_res = [&](int i) {  // the lane's residual of row i, staged above
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        res[i & 1][jj] = *reinterpret_cast<const uint4*>(smem + ((kt1 + (i >> 2)) & 1) * G2_STAGE +
+                                                         (wave * 16 + (i & 3) * 4 + jj) * 512 + el * 8);
+    };
+    if (EPI == EPI_RESIDUAL_STORE) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (this wave's own loads: no barrier)
+      asm volatile("" ::: "memory");
+      if (MI) read_res(0);
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      G2_FENCE;
+      if (EPI == EPI_RESIDUAL_STORE && i + 1 < MI) read_res(i + 1);
+      G2_FENCE;
+      const int gm = m0 + row_of(i);
+      if (EPI == EPI_SWIGLU_STORE) {
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {  // N = ffn_dim (output width); gate in jj, up in jj + 2
+          float g[8], u[8];
+          get(i, jj, g);
+          get(i, jj + 2, u);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) g[e] = g[e] / (1.0f + __expf(-g[e])) * u[e];
+          *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(Cv) + (size_t)gm * N + n0 / 2 + wn * 64 + 32 * jj + ec8) = g2_pack(g);
+        }
+      } else {
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const size_t idx = (size_t)gm * N + n0 + wn * 128 + 32 * jj + ec8;
+          float v[8];
+          get(i, jj, v);
+          if (EPI == EPI_STORE_F32) {
+            float* dst = reinterpret_cast<float*>(Cv) + idx;
+            *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+          } else {
+            float r[8];
+            g2_unpack(res[i & 1][jj], r);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = r[e] + v[e];
+            *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(Cv) + idx) = g2_pack(v);
+          }
+        }
+      }
+    }
+  };
+  if (m0 + 128 + wm * 64 < M)
+    tile(std::integral_constant<int, 8>{});
+  else if (m0 + wm * 64 < M)
+    tile(std::integral_constant<int, 4>{});
+  else
+    tile(std::integral_constant<int, 0>{});
+}
+
+#undef G2_FENCE
+#undef G2_BARRIER
+
 // Epilogue of the tiles that were cut along K: partial slices added in slice order (reproducible).
 template <int BM, int BN, int WM, int WN, int EPI>
 __global__ void __launch_bounds__(256)
@@ -555,6 +1013,14 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+template <int BM, int BN, int WM, int WN, int EPI, int GBK, int NST>
+static auto gemm_kernel() {
+  if constexpr (BM == 256)
+    return k_gemm_256<EPI>;
+  else
+    return k_gemm_mfma<BM, BN, WM, WN, EPI, GBK, NST>;
+}
+
 constexpr size_t GEMM_SPLIT_WS_BYTES = (size_t)256 * 256 * 256 * sizeof(float);  // 256 partial tiles of 256 x 256
 
 template <int BM, int BN, int WM, int WN, int GBK, int NST>
@@ -588,7 +1054,7 @@ static void launch_cfg(const bf16_t* A, int M, int K, const MfmaB& b, const bf16
   float* part = reinterpret_cast<float*>(ws);
 #define GO(E)                                                                                              \
   do {                                                                                                     \
-    auto kern = k_gemm_mfma<BM, BN, WM, WN, E, GBK, NST>;                                                  \
+    auto kern = gemm_kernel<BM, BN, WM, WN, E, GBK, NST>();                                                \
     static std::atomic<uint64_t> attr_done{0};                                                             \
     set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(kern), (int)sh);                        \
     hipLaunchKernelGGL(kern, grid, block, sh, s, A, M, K, b, B2, N, residual, C, tiles_m, tiles_n, full, split, part, qe); \
@@ -627,7 +1093,7 @@ static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
     acc += B.n_rows[p];
     if (acc % 256) return false;
   }
-  if (rows % 256) return false;
+  if (rows % 256 || K < 128) return false;  // (at least two K slices)
   const long tiles_m = (M + 255) / 256, work = tiles_m * (rows / 256) * (K / 64);
   return work >= 10000 || (work >= 8000 && M > 128) || (work >= 4000 && M * 5L >= tiles_m * 256 * 4) ||
          (work >= 3000 && M > 600);
@@ -662,7 +1128,7 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
   const int rows = epilogue == EPI_SWIGLU_STORE ? 2 * N : N;
   const QkvEpilogue qe = qkv ? *qkv : QkvEpilogue{};
   if (big_tiles(M, K, B, rows))
-    launch_cfg<256, 256, 4, 2, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
+    launch_cfg<256, 256, 2, 2, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
   else if (rows % 128 == 0)
     // (a wave as wide as the tile: a head per wave for the fused QKV epilogue, and where weights bound the launch the
     // waves whose rows lie past M drop out sooner: 64 x 5120 x 5120 20.5 us, 65 x 5120 x 27648 71.6 us, against 20.7
