@@ -68,7 +68,7 @@ struct keep_ctx {
   RealignSeg* d_segs = nullptr;
   void *xa = nullptr, *xb = nullptr, *hbuf = nullptr, *q = nullptr, *kc = nullptr, *o = nullptr, *x1 = nullptr,
        *act = nullptr, *attn_scratch = nullptr, *skinny_ws = nullptr;
-  float *qkv_raw = nullptr, *lse = nullptr, *score_scratch = nullptr, *S = nullptr, *sel_tot = nullptr;
+  float *qkv_raw = nullptr, *lse = nullptr, *score_scratch = nullptr, *S = nullptr, *sel_scratch = nullptr;
   int32_t* sel_out = nullptr;
 
   // pinned host
@@ -251,7 +251,7 @@ uint64_t workspace_bytes(const keep_model_desc* d) {
   if (wants_mfma(d)) t += align256(attn_mfma_scratch_bytes((int32_t)z.M, d->n_q_heads, d->n_kv_heads));
   if (wants_mfma(d)) t += align256(gemm_ws_bytes());
   t += align256((z.G + 1) * z.G * sizeof(float));                      // S
-  t += align256((z.G + 1) * sizeof(float));                            // sel_tot
+  t += align256(select_scratch_words((int32_t)z.G) * sizeof(float));   // sel_scratch
   t += align256((z.G + 2) * sizeof(int32_t));                          // sel_out
   t += align256(4 * KEEP_DECODE_MAX_TOKENS * 4) + align256((size_t)d->vocab * sizeof(float));  // decode
   t += align256(ARGMAX_BLOCKS * sizeof(uint64_t));
@@ -651,7 +651,7 @@ SelectKind classify_budget(const PromptInfo& pi, const keep_prompt* p, const int
 }
 
 keep_status enqueue_select(keep_ctx* c, int m, int k_count, int tok_budget, int mode, int hops, hipStream_t s) {
-  launch_select(c->S, m, c->d_cand_len, k_count, tok_budget, mode, hops, c->sel_tot, c->sel_out, s, c->set_only);
+  launch_select(c->S, m, c->d_cand_len, k_count, tok_budget, mode, hops, c->sel_scratch, c->sel_out, s, c->set_only);
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipMemcpyAsync(c->h_sel_out, c->sel_out, (size_t)(m + 2) * 4, hipMemcpyDeviceToHost, s));
   return KEEP_OK;
@@ -909,7 +909,7 @@ keep_status keep_init(const keep_model_desc* desc, const keep_layer_weights* lay
     TRY_INIT(dev_alloc(c, reinterpret_cast<char**>(&c->skinny_ws), gemm_ws_bytes()));
   }
   TRY_INIT(dev_alloc(c, &c->S, (z.G + 1) * z.G * sizeof(float)));
-  TRY_INIT(dev_alloc(c, &c->sel_tot, (z.G + 1) * sizeof(float)));
+  TRY_INIT(dev_alloc(c, &c->sel_scratch, select_scratch_words((int32_t)z.G) * sizeof(float)));
   TRY_INIT(dev_alloc(c, &c->sel_out, (z.G + 2) * 4));
 
   // RoPE table: angle = position * theta^(-2j/head_dim), evaluated in double, stored fp32

@@ -253,9 +253,11 @@ struct SelectPrep {
   int32_t* cand_total;
 };
 
+size_t select_scratch_words(int32_t m);
 // multi-hop selection on the device; d_out: [0] = n_next, [1] = hops_run, [2..] = slots kept (ascending)
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
-                   int32_t mode, int32_t hops, float* d_tot /*[m+1]*/, int32_t* d_out /*[m+2]*/, hipStream_t s,
+                   int32_t mode, int32_t hops, float* d_scratch /*[select_scratch_words(m)], 8-byte aligned*/,
+                   int32_t* d_out /*[m+2]*/, hipStream_t s,
                    bool set_only = false, const SelectPrep* prep = nullptr);
 // set_only: the propagation averages the normalised rows of the relevant set alone (the query's row
 // only initialises the importance); default: the query stays a source at every hop.

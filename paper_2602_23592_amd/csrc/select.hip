@@ -294,6 +294,136 @@ __global__ void __launch_bounds__(SEL_THREADS)
 }
 
 // ---------------------------------------------------------------------------------------------
+// The same selection over several launches, where there are enough candidates that the propagation, one division per
+// listed row and candidate, is worth more than one CU: k_select_step chooses and lists a set (one workgroup), and
+// k_propagate forms the next importances (a workgroup per 64 candidates).  A step that finds the set it was given ends
+// the selection: what is launched behind it returns at once.  Same sums, divisions and orders as in k_select.
+//
+// k_propagate: lane = candidate.  Seven waves fetch the listed rows of a block of 112 and divide, the eighth adds the
+// block before in ascending order: its chain of additions, 8 cycles each, is what bounds the kernel.
+// ---------------------------------------------------------------------------------------------
+constexpr int PR_WAVES = 8, PR_ROWS = 16 * (PR_WAVES - 1);
+
+// scratch of the launches, behind the m + 1 row totals
+struct SelectState {
+  int32_t* flags;  // [4]: selection ended, selections run, members of the set
+  uint64_t* key;   // [m] importances as sort keys
+  int32_t* list;   // [m] the set, ascending
+  uint8_t* rel;    // [m] its members
+};
+static SelectState select_state(float* scratch, int m) {
+  SelectState st;
+  int32_t* w = reinterpret_cast<int32_t*>(scratch) + (m + 1 + 1) / 2 * 2;
+  st.key = reinterpret_cast<uint64_t*>(w);
+  st.flags = w + 2 * m;
+  st.list = st.flags + 4;
+  st.rel = reinterpret_cast<uint8_t*>(st.list + m);
+  return st;
+}
+
+__global__ void __launch_bounds__(PR_WAVES * 64)
+    k_propagate(const float* __restrict__ S, int m, int set_only, const float* __restrict__ row_tot, SelectState st) {
+  __shared__ float s_q[2][PR_ROWS][64];
+  if (st.flags[0]) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.x * 64 + lane, bc = min(b, m - 1);
+  const int n_rel = st.flags[2], n_src = (set_only ? 0 : 1) + n_rel;
+  const int n_blocks = (n_rel + PR_ROWS - 1) / PR_ROWS;
+  const float tq = row_tot[m];
+  float acc = !set_only && tq > 0.f ? S[(size_t)m * m + bc] / tq : 0.f;
+  for (int k = -1; k < n_blocks; ++k) {
+    if (wave < PR_WAVES - 1) {
+      const int i0 = (k + 1) * PR_ROWS + wave * 16;  // 16 consecutive rows of the next block
+      if (i0 < n_rel) {
+        float v[16], t[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          const int a = st.list[min(i0 + u, n_rel - 1)];
+          t[u] = row_tot[a];
+          v[u] = S[(size_t)a * m + bc];
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s_q[(k + 1) & 1][wave * 16 + u][lane] = t[u] > 0.f ? v[u] / t[u] : 0.f;
+      }
+    } else if (k >= 0) {
+      const int rows = min(PR_ROWS, n_rel - k * PR_ROWS);
+      int i = 0;
+      for (; i + 16 <= rows; i += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = s_q[k & 1][i + u][lane];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc = acc + v[u];
+      }
+      for (; i < rows; ++i) acc = acc + s_q[k & 1][i][lane];
+    }
+    __syncthreads();
+  }
+  if (wave == PR_WAVES - 1 && b < m) st.key[b] = sel_key(n_src > 0 ? acc / (float)n_src : acc, b);
+}
+
+__global__ void __launch_bounds__(SEL_THREADS)
+    k_select_step(const float* __restrict__ S, int m, int P, const int32_t* __restrict__ cand_len, int k_count,
+                  int token_budget, int mode, int first, const float* __restrict__ row_tot, SelectState st,
+                  int32_t* __restrict__ out, const int32_t* __restrict__ cand_total, const int32_t* __restrict__ id_map) {
+  extern __shared__ __attribute__((aligned(16))) char sel_smem[];
+  uint64_t* key = reinterpret_cast<uint64_t*>(sel_smem);  // [P]
+  int32_t* list = reinterpret_cast<int32_t*>(key + P);    // [m]
+  int32_t* len = list + m;                                // [m]
+  uint8_t* rel = reinterpret_cast<uint8_t*>(len + m);     // [m]
+  __shared__ int s_diff, s_cnt[SEL_THREADS / 64];
+  if (!first && st.flags[0]) return;
+  if (first && cand_total) {  // (as in k_select)
+    const bool all = m > 0 && (mode == KEEP_BUDGET_GROUP_COUNT ? k_count >= m : token_budget >= *cand_total);
+    const bool none = m == 0 || (mode == KEEP_BUDGET_GROUP_COUNT ? k_count == 0 : token_budget <= 0);
+    if (all || none) {
+      const int n = all ? m : 0;
+      for (int a = threadIdx.x; a < n; a += SEL_THREADS) out[2 + a] = id_map ? id_map[a] : a;
+      if (threadIdx.x == 0) {
+        out[0] = n;
+        out[1] = 0;
+        st.flags[0] = 1;
+      }
+      return;
+    }
+  }
+  const int runs = first ? 1 : st.flags[1] + 1;
+  const float tq = row_tot[m];
+  for (int b = threadIdx.x; b < m; b += SEL_THREADS) {
+    len[b] = cand_len[b];
+    key[b] = first ? sel_key(tq > 0.f ? S[(size_t)m * m + b] / tq : 0.f, b) : st.key[b];
+  }
+  if (threadIdx.x == 0) s_diff = first;
+  take(key, m, P, len, k_count, token_budget, mode, rel);
+  if (!first) {
+    int differs = 0;
+    for (int a = threadIdx.x; a < m; a += SEL_THREADS) differs |= rel[a] != st.rel[a];
+    if (differs) s_diff = 1;  // (every writer writes the same value)
+    __syncthreads();
+  }
+  if (!s_diff) {  // the set repeated: it is listed already
+    if (threadIdx.x == 0) {
+      out[1] = runs;
+      st.flags[0] = 1;
+    }
+    return;
+  }
+  const int n_rel = compact(rel, m, list, s_cnt);
+  for (int a = threadIdx.x; a < m; a += SEL_THREADS) st.rel[a] = rel[a];
+  for (int i = threadIdx.x; i < n_rel; i += SEL_THREADS) {
+    st.list[i] = list[i];
+    out[2 + i] = id_map ? id_map[list[i]] : list[i];
+  }
+  if (threadIdx.x == 0) {
+    out[0] = n_rel;
+    out[1] = runs;
+    st.flags[0] = 0;
+    st.flags[1] = runs;
+    st.flags[2] = n_rel;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // k_select_small: fewer than 64 candidates, one per lane of one wave.
 //
 // Bound by launches and barriers.  Four waves bring S (at most 64 x 63) to LDS, all loads in flight at once, and the
@@ -384,8 +514,17 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// scratch of launch_select in words, for up to m candidates
+size_t select_scratch_words(int32_t m) { return (size_t)(m + 1 + 1) / 2 * 2 + (size_t)3 * m + 4 + (size_t)(m + 3) / 4; }
+
+// From here on the propagation gets workgroups of its own.  Back to back, us for a call of two / three / three / four
+// selections that keep 5 / 10 / 15 / 40 % of the candidates: 512 candidates 31 / 53 / 54 / 110 in one workgroup against
+// 34 / 56 / 52 / 89, 768: 40 / 74 / 72 / 170 against 42 / 71 / 65 / 112, 1024: 44 / 87 / 90 / 236 against
+// 44 / 75 / 69 / 126, 4000: 202 / 581 / 741 / 2673 against 106 / 197 / 170 / 366.
+constexpr int SEL_SPREAD = 900;
+
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
-                   int32_t mode, int32_t hops, float* d_tot, int32_t* d_out, hipStream_t s, bool set_only,
+                   int32_t mode, int32_t hops, float* d_scratch, int32_t* d_out, hipStream_t s, bool set_only,
                    const SelectPrep* prep) {
   const SelectPrep pr = prep ? *prep : SelectPrep{};
   if (m < SEL_SMALL) {
@@ -395,13 +534,27 @@ void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t
   }
   int P = 2;
   while (P < m) P <<= 1;
+  const int blocks = (m + 1 + RT_ROWS - 1) / RT_ROWS + (prep ? 1 : 0);
+  hipLaunchKernelGGL(k_row_totals, dim3(blocks), dim3(RT_THREADS), 0, s, S, m, d_scratch, pr);
+  const int max_runs = hops > 1 ? hops : 1;
+  if (max_runs > 1 && m >= SEL_SPREAD) {
+    const SelectState st = select_state(d_scratch, m);
+    const size_t sh = (size_t)P * 8 + (size_t)m * (2 * 4 + 1);
+    static std::atomic<uint64_t> attr_done{0};
+    set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select_step), 160 * 1024 - 256);
+    for (int run = 1; run <= max_runs; ++run) {
+      if (run > 1)
+        hipLaunchKernelGGL(k_propagate, dim3((m + 63) / 64), dim3(PR_WAVES * 64), 0, s, S, m, set_only ? 1 : 0, d_scratch, st);
+      hipLaunchKernelGGL(k_select_step, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode,
+                         run == 1 ? 1 : 0, d_scratch, st, d_out, pr.cand_total, pr.groups);
+    }
+    return;
+  }
   const size_t sh = (size_t)P * 8 + (size_t)m * (3 * 4 + 2);  // <= 147 KB: m <= 6000
   static std::atomic<uint64_t> attr_done{0};
   set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select), 160 * 1024 - 256);
-  const int blocks = (m + 1 + RT_ROWS - 1) / RT_ROWS + (prep ? 1 : 0);
-  hipLaunchKernelGGL(k_row_totals, dim3(blocks), dim3(RT_THREADS), 0, s, S, m, d_tot, pr);
   hipLaunchKernelGGL(k_select, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode, hops,
-                     set_only ? 1 : 0, d_tot, d_out, pr.cand_total, pr.groups);
+                     set_only ? 1 : 0, d_scratch, d_out, pr.cand_total, pr.groups);
 }
 
 }  // namespace keep

@@ -1,8 +1,8 @@
 // keep_select_groups_static: the multi-hop selection for callers that cannot allocate.
 //
 // Same kernels as keep_select_groups (k_select_small; from 64 candidates on k_row_totals, k_select).  That entry point
-// keeps the candidates' lengths, their token total and the row totals in the context's workspace (device memory the
-// library allocated at keep_init);
+// keeps the candidates' lengths, their token total and the selection's scratch in the context's workspace (device memory
+// the library allocated at keep_init);
 // here they live in a file-scope device array, so the call needs no context, no workspace and makes no
 // allocation of any kind.  Every GPU the library runs on holds its own copy of the array until the process
 // ends; all calls on one GPU share it, so calls that overlap on one GPU race.
@@ -21,10 +21,10 @@ using namespace keep;
 
 namespace {
 
-// scratch: [0, KEEP_STATIC_MAX_CANDIDATES) lengths of the candidates, one word: their sum, and from SCRATCH_TOTALS on
-// the row totals of S (floats)
-constexpr int SCRATCH_TOTALS = KEEP_STATIC_MAX_CANDIDATES + 64;
-constexpr int SCRATCH_WORDS = SCRATCH_TOTALS + KEEP_STATIC_MAX_CANDIDATES + 64;
+// scratch: [0, KEEP_STATIC_MAX_CANDIDATES) lengths of the candidates, one word: their sum, and from SCRATCH_SELECT on
+// what the selection keeps between its launches (select_scratch_words: four and a quarter words per candidate)
+constexpr int SCRATCH_SELECT = KEEP_STATIC_MAX_CANDIDATES + 64;
+constexpr int SCRATCH_WORDS = SCRATCH_SELECT + 5 * KEEP_STATIC_MAX_CANDIDATES;
 static __device__ __align__(256) int32_t scratch[SCRATCH_WORDS];
 
 constexpr int MAX_DEVICES = 64;
@@ -82,7 +82,7 @@ extern "C" keep_status keep_select_groups_static(const float* S, const int32_t* 
   const int token_budget = (int)floor((double)ratio_next * (double)mem_tokens + 1.0e-3);
   const SelectPrep prep{groups, group_len, n_groups_total, cand_len, cand_total};
   launch_select(S, n_sel, cand_len, k_count, token_budget, budget_mode, hops,
-                reinterpret_cast<float*>(sp + SCRATCH_TOTALS), result, s,
+                reinterpret_cast<float*>(sp + SCRATCH_SELECT), result, s,
                 propagation_sources == KEEP_SOURCES_SET_ONLY, &prep);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_static(KEEP_ERR_HIP, hipGetErrorString(e));
