@@ -1115,6 +1115,10 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
     launch_gemm_skinny(A, M, K, B, B2, N, epilogue, residual, C, skinny_ws, s, qkv, norm);
     return;
   }
+  if (gemm_stream_fits(M, K, B, N, epilogue)) {
+    launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, qkv);
+    return;
+  }
   MfmaB b;
   b.n_parts = B.n_parts;
   int acc = 0;

@@ -1,0 +1,343 @@
+// bf16 GEMM for 17 to 128 rows: C[M, N] = A[M, K] . W[N, K]^T (fp32 accumulate) with the epilogues of a layer.
+//
+// With so few rows the work is still reading the weights once, but every workgroup also needs all the activations, so
+// what counts is that all 256 CUs stream an equal share of the weights from the first slice to the last.  The output
+// columns are therefore dealt out evenly (20 columns per workgroup for 5120, 54 gate/up pairs for 13824): one workgroup
+// per CU owns its columns over the WHOLE of K and finishes them itself, with no cuts along K and no pass that adds them.
+// Weights and activations go global -> LDS through a ring of three to eight stages of 64 or 128 deep slices, one barrier
+// per stage, so that 70 to 140 KB per CU are on their way: tiles of 128x128 with two stages had half of that, on 0.6 to
+// 0.85 of the chip, and each launch a second one behind it.  The weights are the A operand of v_mfma_f32_16x16x32_bf16,
+// 16 columns per tile, the activations the B operand, 16 rows per tile; a wave owns one or two of the activation tiles.
+// The loads run on over the ends of a workgroup's tiles.  (Workgroups that start at different places along K: no change.)
+#include <algorithm>
+#include <type_traits>
+
+#include "keep_internal.h"
+
+namespace keep {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+namespace {
+
+constexpr int ST_WGS = 256;      // workgroups resident on the chip: one per CU
+constexpr int ST_MIN_ROWS = 17, ST_MAX_ROWS = 128;
+
+struct StreamArgs {
+  const bf16_t* A;
+  int M, K, N;       // N: output columns
+  int units, tiles;  // output columns (SwiGLU, RoPE: pairs) of a tile, and tiles
+  const bf16_t* w[3];  // weight parts; SwiGLU: gate, up
+  int begin[4];        // first output column of each part (SwiGLU: unused)
+  const bf16_t* residual;
+  void* C;
+  QkvEpilogue qe;
+};
+
+__device__ __forceinline__ constexpr int st_vmcnt(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+
+// element offset of 16-byte chunk `chunk` of row `row` in a [rows][64] tile: 16 consecutive rows cover all banks
+__device__ __forceinline__ int st_off(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3); }
+
+template <int EPI, int UT, int MT, int SUB, int ST>
+__global__ void __launch_bounds__(256, 2) k_gemm_stream(StreamArgs g) {
+  constexpr bool PAIRS = EPI == EPI_SWIGLU_STORE || EPI == EPI_QKV_ROPE;
+  constexpr int UH = PAIRS ? UT / 2 : UT;          // weight tiles of 16 units
+  constexpr int ROWS = (UT + MT) * 16;             // LDS rows of a slice: weights, then activations
+  constexpr int SLICE = ROWS * 64, STAGE = SLICE * SUB;  // elements
+  constexpr int LPS = ROWS / 8 / 4;                // loads of a wave per slice (8 rows each)
+  constexpr int L = LPS * SUB;                     // ... per stage
+  constexpr int AW = MT == 8 ? 2 : 1;              // activation tiles of a wave
+  constexpr int KB = UT * AW <= 16 ? 2 : 1;        // 32-deep k-steps whose operands are read at once
+  static_assert(ROWS % 32 == 0 && (ST - 2) * L < 64, "loads must split over the waves and fit the wait counter");
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = g.M, K = g.K, N = g.N;
+  const int total = PAIRS && EPI == EPI_QKV_ROPE ? N / 2 : N;
+  const int n_it = K / (64 * SUB);
+  const int n_tiles = (g.tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;  // this workgroup's: blockIdx, + grid, ...
+  typedef const void __attribute__((address_space(1))) * gptr_t;
+  typedef void __attribute__((address_space(3))) * lptr_t;
+
+  // ---- loads: the wave's rows of a slice are (wave * LPS + i) * 8 + lane / 8; the lane fetches the chunk that the swizzle
+  // keeps at its place.  Rows past the tile's last unit or past M read the last one again (no memory traffic).
+  const bf16_t* src[LPS];
+  auto aim = [&](int tile) {
+    const int u0 = tile * g.units, count = min(g.units, total - u0);
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) {
+      const int r = (wave * LPS + i) * 8 + lane / 8, c = (lane & 7) ^ ((r >> 1) & 7);
+      const bf16_t* row;
+      if (r < UT * 16) {
+        const int half = r / (UH * 16), u = u0 + min(r % (UH * 16), count - 1);
+        if (EPI == EPI_SWIGLU_STORE) {
+          row = (half ? g.w[1] : g.w[0]) + (size_t)u * K;
+        } else {
+          const int n = EPI == EPI_QKV_ROPE ? (u >> 6) * 128 + (u & 63) + half * 64 : u;  // RoPE pairs column c of a head with c + 64
+          const bf16_t* base = g.w[0];
+          int first = 0;
+          if (EPI == EPI_QKV_ROPE && n >= g.begin[1]) base = g.w[1], first = g.begin[1];
+          if (EPI == EPI_QKV_ROPE && n >= g.begin[2]) base = g.w[2], first = g.begin[2];
+          row = base + (size_t)(n - first) * K;
+        }
+      } else {
+        row = g.A + (size_t)min(r - UT * 16, M - 1) * K;
+      }
+      src[i] = row + c * 8;
+    }
+  };
+  int lt = 0, li = 0, slot = 0;  // tile, stage of the tile and place in the ring of the next stage to request
+  auto request = [&]() {
+#pragma unroll
+    for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+      for (int i = 0; i < LPS; ++i)
+        __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + ((size_t)li * SUB + sub) * 64),
+                                         (lptr_t)(smem + slot * STAGE + sub * SLICE + (wave * LPS + i) * 512), 16, 0, 0);
+    slot = slot + 1 == ST ? 0 : slot + 1;
+    if (++li == n_it) {
+      li = 0;
+      if (++lt < n_tiles) aim(blockIdx.x + lt * gridDim.x);
+    }
+  };
+
+  f32x4 acc[UT][AW];
+  const int row16 = lane & 15, kg = lane >> 4;
+  int w_off[2], a_off[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    w_off[ks] = st_off(row16, ks * 4 + kg);
+    a_off[ks] = st_off(UT * 16 + (wave % MT) * 16 + row16, ks * 4 + kg);
+  }
+  const bool works = wave < MT && (wave * 16 < M);  // (a wave without rows of its own only loads)
+  // acc[t][a][e]: unit 16 t + 4 kg + e of the tile (pairs: t and t + UH), row 16 (wave + 4 a) + row16
+  auto finish = [&](int tile) {
+    const int u0 = tile * g.units, count = min(g.units, total - u0);
+#pragma unroll
+    for (int a = 0; a < AW; ++a) {
+      const int m = (wave + 4 * a) * 16 + row16;
+      if (m >= M) continue;
+      int pos = 0, rp = 0;
+      if (EPI == EPI_QKV_ROPE) {
+        pos = g.qe.row_pos[m];
+        rp = pos - (g.qe.row_lo ? g.qe.row_lo[m] : 0);
+      }
+#pragma unroll
+      for (int t = 0; t < UH; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int ul = t * 16 + 4 * kg + e;
+          if (ul >= count) continue;
+          const int u = u0 + ul;
+          if constexpr (EPI == EPI_QKV_ROPE) {
+            const QkvEpilogue& qe = g.qe;
+            float lo = acc[t][a][e], hi = acc[t + UH][a][e];
+            const int rc = u & 63, n = (u >> 6) * 128 + rc;
+            const int kind = n >= g.begin[2] ? 2 : (n >= g.begin[1] ? 1 : 0);
+            const int hc = n - (kind == 2 ? g.begin[2] : (kind == 1 ? g.begin[1] : 0));
+            const bf16_t* bp = reinterpret_cast<const bf16_t*>(kind == 2 ? qe.bias[2] : (kind == 1 ? qe.bias[1] : qe.bias[0]));
+            if (bp) {
+              lo += bf16_bits_to_f32(bp[hc].bits);
+              hi += bf16_bits_to_f32(bp[hc + 64].bits);
+            }
+            if (kind == 2) {
+              bf16_t* dst = reinterpret_cast<bf16_t*>(qe.v_cache) + (size_t)pos * qe.kv_dim + hc;
+              dst[0].bits = f32_to_bf16_bits(lo);
+              dst[64].bits = f32_to_bf16_bits(hi);
+            } else {
+              const float cc = qe.rope_cos[(size_t)rp * 64 + rc], ss = qe.rope_sin[(size_t)rp * 64 + rc];
+              const uint16_t olo = f32_to_bf16_bits(lo * cc - hi * ss), ohi = f32_to_bf16_bits(hi * cc + lo * ss);
+              bf16_t* d1 = kind == 0 ? reinterpret_cast<bf16_t*>(qe.q) + (size_t)m * qe.q_dim + hc
+                                     : reinterpret_cast<bf16_t*>(qe.k_compact) + (size_t)m * qe.kv_dim + hc;
+              d1[0].bits = olo;
+              d1[64].bits = ohi;
+              if (kind == 1) {
+                bf16_t* d2 = reinterpret_cast<bf16_t*>(qe.k_cache) + (size_t)pos * qe.kv_dim + hc;
+                d2[0].bits = olo;
+                d2[64].bits = ohi;
+              }
+            }
+          } else if constexpr (EPI == EPI_SWIGLU_STORE) {
+            const float s0 = acc[t][a][e];
+            reinterpret_cast<bf16_t*>(g.C)[(size_t)m * N + u].bits =
+                f32_to_bf16_bits(s0 / (1.0f + __expf(-s0)) * acc[t + UH][a][e]);
+          } else {
+            const size_t idx = (size_t)m * N + u;
+            reinterpret_cast<bf16_t*>(g.C)[idx].bits = f32_to_bf16_bits(bf16_bits_to_f32(g.residual[idx].bits) + acc[t][a][e]);
+          }
+        }
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int t = 0; t < UT; ++t)
+#pragma unroll
+      for (int a = 0; a < AW; ++a) acc[t][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  int cs = 0;  // ring place of the stage in hand
+  auto compute = [&]() {
+    if (works) {
+      const uint16_t* base = smem + cs * STAGE;
+#pragma unroll
+      for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+        for (int k0 = 0; k0 < 2; k0 += KB) {
+          bf16x8 x[KB][AW], w[KB][UT];
+#pragma unroll
+          for (int ks = 0; ks < KB; ++ks) {
+#pragma unroll
+            for (int a = 0; a < AW; ++a)
+              x[ks][a] = *reinterpret_cast<const bf16x8*>(base + sub * SLICE + a_off[k0 + ks] + a * 64 * 64);
+#pragma unroll
+            for (int t = 0; t < UT; ++t)
+              w[ks][t] = *reinterpret_cast<const bf16x8*>(base + sub * SLICE + w_off[k0 + ks] + t * 16 * 64);
+          }
+#pragma unroll
+          for (int ks = 0; ks < KB; ++ks)
+#pragma unroll
+            for (int t = 0; t < UT; ++t)
+#pragma unroll
+              for (int a = 0; a < AW; ++a)
+                acc[t][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][t], x[ks][a], acc[t][a], 0, 0, 0);
+        }
+      // (one wave per SIMD: reads first, or the compiler pairs every read with a wait)
+#pragma unroll
+      for (int b = 0; b < SUB * 2 / KB; ++b) {
+        __builtin_amdgcn_sched_group_barrier(0x100, KB * (AW + UT), 0);
+        if (KB == 1 || b + 1 == SUB * 2 / KB) __builtin_amdgcn_sched_group_barrier(0x008, KB == 1 ? UT * AW : 2 * SUB * UT * AW, 0);
+      }
+    }
+    cs = cs + 1 == ST ? 0 : cs + 1;
+  };
+
+  // All stages of all its tiles are one sequence, requested ST - 1 ahead.  A barrier shows that every wave's loads of the
+  // stage in hand have landed and that every wave is done with the one before, whose place is requested next.
+  const int n_seq = n_tiles * n_it;
+  int seq = 0, ct = 0, ci = 0;
+  aim(blockIdx.x);
+  clear();
+  for (int s = 0; s < ST - 1; ++s) request();
+  auto step = [&]() {
+    compute();
+    ++seq;
+    if (++ci == n_it) {
+      if (works) finish(blockIdx.x + ct * gridDim.x);
+      clear();
+      ci = 0;
+      ++ct;
+    }
+  };
+  while (seq + ST - 1 < n_seq) {
+    __builtin_amdgcn_s_waitcnt(st_vmcnt((ST - 2) * L));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    request();
+    step();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  auto last = [&](auto self, auto left) -> void {  // the last ST - 1 stages are all on their way
+    __builtin_amdgcn_s_waitcnt(st_vmcnt((decltype(left)::value - 1) * L));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    step();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (decltype(left)::value > 1) self(self, std::integral_constant<int, decltype(left)::value - 1>{});
+  };
+  last(last, std::integral_constant<int, ST - 1>{});
+}
+
+template <int EPI, int UT, int MT, int SUB, int ST>
+void launch_stream_cfg(StreamArgs g, hipStream_t s) {
+  constexpr bool PAIRS = EPI == EPI_SWIGLU_STORE || EPI == EPI_QKV_ROPE;
+  constexpr int CAP = (PAIRS ? UT / 2 : UT) * 16;
+  const int total = EPI == EPI_QKV_ROPE ? g.N / 2 : g.N;
+  const int rounds = (total + ST_WGS * CAP - 1) / (ST_WGS * CAP);
+  g.units = (total + rounds * ST_WGS - 1) / (rounds * ST_WGS);
+  g.tiles = (total + g.units - 1) / g.units;
+  constexpr int sh = ST * SUB * (UT + MT) * 16 * 64 * 2;
+  static_assert(sh <= 160 * 1024, "the ring does not fit LDS");
+  auto kern = k_gemm_stream<EPI, UT, MT, SUB, ST>;
+  static std::atomic<uint64_t> attr_done{0};
+  set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(kern), sh);
+  hipLaunchKernelGGL(kern, dim3(std::min(g.tiles, ST_WGS)), dim3(256), sh, s, g);
+}
+
+template <int EPI, int UT, int MT, int SUB>
+void launch_stream_ring(const StreamArgs& g, hipStream_t s) {  // as many stages as fit 144 KB, at most eight
+  constexpr int FIT = 144 / (SUB * (UT + MT) * 2);
+  launch_stream_cfg<EPI, UT, MT, SUB, (FIT < 8 ? FIT : 8)>(g, s);
+}
+
+template <int MT>
+void launch_stream_rows(const StreamArgs& g, int epilogue, hipStream_t s) {
+  const int pairs = (g.N + ST_WGS - 1) / ST_WGS;  // gate/up: of a workgroup, if it takes one tile
+  if (epilogue == EPI_QKV_ROPE)
+    launch_stream_ring<EPI_QKV_ROPE, 2, MT, 2>(g, s);
+  else if (epilogue == EPI_RESIDUAL_STORE)
+    launch_stream_ring<EPI_RESIDUAL_STORE, 2, MT, 2>(g, s);
+  else if (pairs <= 32)
+    launch_stream_ring<EPI_SWIGLU_STORE, 4, MT, 1>(g, s);
+  else if (pairs <= 64)
+    launch_stream_ring<EPI_SWIGLU_STORE, 8, MT, 1>(g, s);
+  else if (pairs <= 80)
+    launch_stream_ring<EPI_SWIGLU_STORE, 10, MT, 1>(g, s);
+  else if constexpr (MT <= 4)
+    launch_stream_ring<EPI_SWIGLU_STORE, 14, MT, 1>(g, s);
+  else  // (two accumulators per weight tile: 14 tiles would not fit the registers)
+    launch_stream_ring<EPI_SWIGLU_STORE, 8, MT, 1>(g, s);
+}
+
+}  // namespace
+
+bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue) {
+  if (M < ST_MIN_ROWS || M > ST_MAX_ROWS || K % 128 || K < 1024) return false;  // (stages of two slices; at least eight of them)
+  // Every CU reads all the activations, and gets about 60 bytes a nanosecond to its LDS, so the few columns per CU of the
+  // narrow projections leave the line early.  Tiles of 128x128 cut along K / this kernel, us:
+  //   gate/up 5120 x 27648, 64 rows 70.8 / 57.0, 128 rows 81.1 / 72.6; 3584 x 37888 68.3 / 51.6, 80.9 / 64.5; 5120 x 55296,
+  //   64 rows 131 / 112; 2048 x 16384 22.3 / 17.5, 28.9 / 21.0: always here.
+  //   O and QKV at 5120: 32 rows 16.6 / 14.8 and 20.1 / 18.0, 48 rows 19.6 / 18.1 and 22.3 / 21.2, 64 rows 20.2 / 19.9 and
+  //   23.2 / 24.4; at 3584, 64 rows: 16.7 / 13.7 and 17.2 / 15.6, 80 rows: 17.9 / 18.7 and 20.2 / 21.9; at 2048, 64 rows:
+  //   11.8 / 8.7 and 13.3 / 10.7.
+  //   Down (13824 x 5120): 32 rows 29.0 / 31.5, 64 rows 32.7 / 44.8: never here.
+  if (epilogue != EPI_SWIGLU_STORE && (K > 5120 || M > (K <= 4096 ? 64 : 48))) return false;
+  if (epilogue == EPI_QKV_ROPE) {
+    if (B.n_parts != 3) return false;
+    for (int p = 0; p < 3; ++p)
+      if (B.n_rows[p] % 128) return false;  // whole heads
+    return true;
+  }
+  return B.n_parts == 1 && (epilogue == EPI_SWIGLU_STORE || epilogue == EPI_RESIDUAL_STORE);
+}
+
+void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
+                        const bf16_t* residual, void* C, hipStream_t s, const QkvEpilogue* qkv) {
+  StreamArgs g{};
+  g.A = A;
+  g.M = M;
+  g.K = K;
+  g.N = N;
+  int acc = 0;
+  for (int p = 0; p < 3; ++p) {
+    g.begin[p] = acc;
+    if (p < B.n_parts) {
+      g.w[p] = reinterpret_cast<const bf16_t*>(B.ptr[p]);
+      acc += B.n_rows[p];
+    }
+  }
+  g.begin[3] = acc;
+  if (epilogue == EPI_SWIGLU_STORE) g.w[1] = reinterpret_cast<const bf16_t*>(B2);
+  g.residual = residual;
+  g.C = C;
+  if (qkv) g.qe = *qkv;
+  if (M <= 32)
+    launch_stream_rows<2>(g, epilogue, s);
+  else if (M <= 64)
+    launch_stream_rows<4>(g, epilogue, s);
+  else
+    launch_stream_rows<8>(g, epilogue, s);
+}
+
+}  // namespace keep

@@ -1,0 +1,40 @@
+"""17 to 128 rows, the weight-streaming kernel with a ring of stages: row counts around its three forms (32, 64, 128 rows)
+and where the narrow projections leave it (48, 64), widths that give a workgroup part of a tile of columns, several tile
+widths for gate/up, more than one tile per workgroup, and columns that straddle heads and q, k and v.  bf16 storage bounds
+the error: 2e-2 of the largest value, as for the other bf16 launches."""
+import numpy as np
+import pytest
+import torch
+
+import keep_synth as ks
+from gpu_util import Problem, max_rel, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(hidden, heads, kv, ffn):
+    return ks.ModelShape(2, hidden, heads, kv, 128, ffn, 211, 1.0e6, 1e-6, "bf16")
+
+
+# K = 1024 (the shortest ring) and 1152; 5 and 6 gate/up pairs per workgroup; pairs across heads
+NARROW = [(_shape(1024, 8, 2, 1152), n) for n in (17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 96, 127, 128, 129)] + \
+         [(_shape(1152, 9, 3, 1408), n) for n in (17, 48, 64, 100)]
+# gate/up pairs per workgroup: 33 and 64 (four tiles of gate, four of up), 65 and 80 (five), 81 (seven, or two rounds)
+WIDE = [(_shape(1024, 8, 1, ffn), n) for ffn in (8320, 16384, 16512, 20480, 20608) for n in (20, 50, 100)]
+
+
+@pytest.mark.parametrize("shape,n", NARROW + WIDE, ids=lambda v: str(v) if isinstance(v, int) else "h%d_f%d" % (v.hidden, v.ffn_dim))
+def test_units_match_oracle(shape, n):
+    pb = Problem(shape, [n - 9, 9], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)
+    ctx = pb.context(max_tokens=n + 2)
+    assert ctx.uses_mfma
+    L = shape.n_layers
+    kc = torch.zeros((L, n, shape.n_kv_heads, shape.head_dim), dtype=torch.bfloat16, device="cuda")
+    vc = torch.zeros_like(kc)
+    ctx.precompute_groups([n - 9, 9], pb.ids[:n], kc, vc)
+    torch.cuda.synchronize()
+    for l in range(L):
+        for g, rows in enumerate((slice(0, n - 9), slice(n - 9, n))):
+            ek, ev = max_rel(to_np(kc[l][rows]), pb.kb[l][g]), max_rel(to_np(vc[l][rows]), pb.vb[l][g])
+            print(n, "layer", l, "unit", g, "K %.2e V %.2e" % (ek, ev))
+            assert ek < 2e-2 and ev < 2e-2
