@@ -1,4 +1,4 @@
-// bf16 GEMM for 17 to 128 rows: C[M, N] = A[M, K] . W[N, K]^T (fp32 accumulate) with the epilogues of a layer.
+// bf16 GEMM for 8 to 128 rows: C[M, N] = A[M, K] . W[N, K]^T (fp32 accumulate) with the epilogues of a layer.
 //
 // With so few rows the work is still reading the weights once, but every workgroup also needs all the activations, so
 // what counts is that all 256 CUs stream an equal share of the weights from the first slice to the last.  The output
@@ -22,7 +22,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 namespace {
 
 constexpr int ST_WGS = 256;      // workgroups resident on the chip: one per CU
-constexpr int ST_MIN_ROWS = 17, ST_MAX_ROWS = 128;
+constexpr int ST_MAX_ROWS = 128;
 
 struct StreamArgs {
   const bf16_t* A;
@@ -293,16 +293,31 @@ void launch_stream_rows(const StreamArgs& g, int epilogue, hipStream_t s) {
 }  // namespace
 
 bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue) {
-  if (M < ST_MIN_ROWS || M > ST_MAX_ROWS || K % 128 || K < 1024) return false;  // (stages of two slices; at least eight of them)
-  // Every CU reads all the activations, and gets about 60 bytes a nanosecond to its LDS, so the few columns per CU of the
-  // narrow projections leave the line early.  Tiles of 128x128 cut along K / this kernel, us:
-  //   gate/up 5120 x 27648, 64 rows 70.8 / 57.0, 128 rows 81.1 / 72.6; 3584 x 37888 68.3 / 51.6, 80.9 / 64.5; 5120 x 55296,
-  //   64 rows 131 / 112; 2048 x 16384 22.3 / 17.5, 28.9 / 21.0: always here.
-  //   O and QKV at 5120: 32 rows 16.6 / 14.8 and 20.1 / 18.0, 48 rows 19.6 / 18.1 and 22.3 / 21.2, 64 rows 20.2 / 19.9 and
-  //   23.2 / 24.4; at 3584, 64 rows: 16.7 / 13.7 and 17.2 / 15.6, 80 rows: 17.9 / 18.7 and 20.2 / 21.9; at 2048, 64 rows:
-  //   11.8 / 8.7 and 13.3 / 10.7.
-  //   Down (13824 x 5120): 32 rows 29.0 / 31.5, 64 rows 32.7 / 44.8: never here.
-  if (epilogue != EPI_SWIGLU_STORE && (K > 5120 || M > (K <= 4096 ? 64 : 48))) return false;
+  if (M > ST_MAX_ROWS || K % 128 || K < 1024) return false;  // (stages of two slices; at least eight of them)
+  if (B.has_w4 && M <= 48) return false;                     // (the 4-bit form is read)
+  // Up to 16 rows k_gemv streams as well, with every wave's activations from L2 beside its weights, us, k_gemv / this kernel:
+  //   gate/up 5120 x 27648: 4 rows 49.8 / 50.4, 8 rows 51.1 / 50.5, 16 rows 54.2 / 50.6; 3584 x 37888: 8 rows 49.8 / 48.3,
+  //   16 rows 53.9 / 48.3; but 5120 x 55296: 13 rows 103.6 / 104.9, 16 rows 108.0 / 105.5.
+  //   QKV at 5120: 4 rows 16.0 / 15.5, 8 rows 17.0 / 15.6, 16 rows 18.9 / 16.2; at 3584: 8 rows 12.2 / 11.6, 16 rows 13.5 /
+  //   11.8; but at 2048, 16 rows: 7.7 / 8.3.
+  //   Down 13824 x 5120: 8 rows 28.5 / 30.3, 12 rows 30.6 / 30.4, 16 rows 32.9 / 30.6; 27648 x 5120: 13 rows 58.6 / 57.7, 16
+  //   rows 62.8 / 57.7; O at 5120: 12 rows 13.5 / 13.7, 16 rows 14.4 / 13.9; but 18944 x 3584, 16 rows: 38.5 / 39.6, 3584 x
+  //   3584, 13 rows: 10.1 / 10.2.
+  if (M <= 16) {
+    if (epilogue == EPI_SWIGLU_STORE ? M < 8 || K < 3584 || N > 80 * ST_WGS
+                                     : (epilogue == EPI_QKV_ROPE ? M < 8 || K < 3584 : M < 13 || K < 5120 || N < 5120))
+      return false;
+  } else if (epilogue != EPI_SWIGLU_STORE && (K > 5120 || M > (K <= 4096 ? 64 : 48))) {
+    // Every CU reads all the activations, and gets about 60 bytes a nanosecond to its LDS, so the few columns per CU of the
+    // narrow projections leave the line early.  Tiles of 128x128 cut along K / this kernel, us:
+    //   gate/up 5120 x 27648, 64 rows 70.8 / 57.0, 128 rows 81.1 / 72.6; 3584 x 37888 68.3 / 51.6, 80.9 / 64.5; 5120 x 55296,
+    //   64 rows 131 / 112; 2048 x 16384 22.3 / 17.5, 28.9 / 21.0: always here.
+    //   O and QKV at 5120: 32 rows 16.6 / 14.8 and 20.1 / 18.0, 48 rows 19.6 / 18.1 and 22.3 / 21.2, 64 rows 20.2 / 19.9 and
+    //   23.2 / 24.4; at 3584, 64 rows: 16.7 / 13.7 and 17.2 / 15.6, 80 rows: 17.9 / 18.7 and 20.2 / 21.9; at 2048, 64 rows:
+    //   11.8 / 8.7 and 13.3 / 10.7.
+    //   Down (13824 x 5120): 32 rows 29.0 / 31.5, 64 rows 32.7 / 44.8: not here.
+    return false;
+  }
   if (epilogue == EPI_QKV_ROPE) {
     if (B.n_parts != 3) return false;
     for (int p = 0; p < 3; ++p)

@@ -206,7 +206,7 @@ bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
 void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                         const bf16_t* residual, void* C, void* ws, hipStream_t s, const QkvEpilogue* qkv,
                         const RowNorm* norm);
-// 17 to 128 rows of bf16 weights, all epilogues but the plain store
+// 8 to 128 rows of bf16 weights, all epilogues but the plain store; where it is the fastest
 bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue);
 void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                         const bf16_t* residual, void* C, hipStream_t s, const QkvEpilogue* qkv);

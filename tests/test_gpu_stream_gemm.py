@@ -1,4 +1,4 @@
-"""17 to 128 rows, the weight-streaming kernel with a ring of stages: row counts around its three forms (32, 64, 128 rows)
+"""8 to 128 rows, the weight-streaming kernel with a ring of stages: row counts around its three forms (32, 64, 128 rows)
 and where the narrow projections leave it (48, 64), widths that give a workgroup part of a tile of columns, several tile
 widths for gate/up, more than one tile per workgroup, and columns that straddle heads and q, k and v.  bf16 storage bounds
 the error: 2e-2 of the largest value, as for the other bf16 launches."""
@@ -23,7 +23,11 @@ NARROW = [(_shape(1024, 8, 2, 1152), n) for n in (17, 31, 32, 33, 47, 48, 49, 63
 WIDE = [(_shape(1024, 8, 1, ffn), n) for ffn in (8320, 16384, 16512, 20480, 20608) for n in (20, 50, 100)]
 
 
-@pytest.mark.parametrize("shape,n", NARROW + WIDE, ids=lambda v: str(v) if isinstance(v, int) else "h%d_f%d" % (v.hidden, v.ffn_dim))
+# up to 16 rows, where a shape is wide enough: gate/up and QKV from 8 rows on, O and down from 13
+FEW = [(_shape(5120, 40, 8, 5376), n) for n in (10, 12, 13, 16)]
+
+
+@pytest.mark.parametrize("shape,n", NARROW + WIDE + FEW, ids=lambda v: str(v) if isinstance(v, int) else "h%d_f%d" % (v.hidden, v.ffn_dim))
 def test_units_match_oracle(shape, n):
     pb = Problem(shape, [n - 9, 9], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)
     ctx = pb.context(max_tokens=n + 2)
