@@ -1111,8 +1111,8 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws, const QkvEpilogue* qkv,
                       const RowNorm* norm) {
   if (M <= 0 || N <= 0) return;
-  if (gemm_stream_fits(M, K, B, N, epilogue)) {
-    launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, qkv);
+  if (gemm_stream_fits(M, K, B, N, epilogue, skinny_ws != nullptr)) {
+    launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, skinny_ws, qkv);
     return;
   }
   if (skinny_ws && gemm_skinny_fits(M, K, B, N, epilogue)) {

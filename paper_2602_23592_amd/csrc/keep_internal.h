@@ -207,9 +207,9 @@ void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, c
                         const bf16_t* residual, void* C, void* ws, hipStream_t s, const QkvEpilogue* qkv,
                         const RowNorm* norm);
 // 8 to 128 rows of bf16 weights, all epilogues but the plain store; where it is the fastest
-bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue);
+bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
 void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
-                        const bf16_t* residual, void* C, hipStream_t s, const QkvEpilogue* qkv);
+                        const bf16_t* residual, void* C, hipStream_t s, void* ws, const QkvEpilogue* qkv);
 // h_row_start / h_set_off / m / instr_off: the host copy of the layer's row layout (as for
 // launch_build_rows), from which the work list is planned; h_stage: pinned host ints
 // (attn_mfma_stage_ints), d_scratch: device bytes (attn_mfma_scratch_bytes).

@@ -1,7 +1,7 @@
 """8 to 128 rows, the weight-streaming kernel with a ring of stages: row counts around its three forms (32, 64, 128 rows)
-and where the narrow projections leave it (48, 64), widths that give a workgroup part of a tile of columns, several tile
-widths for gate/up, more than one tile per workgroup, and columns that straddle heads and q, k and v.  bf16 storage bounds
-the error: 2e-2 of the largest value, as for the other bf16 launches."""
+and where the narrow projections are cut along K (8, 17, 33, 64), widths that give a workgroup part of a tile of columns,
+several tile widths for gate/up, more than one tile per workgroup, and columns that straddle heads and q, k and v.  bf16
+storage bounds the error: 2e-2 of the largest value, as for the other bf16 launches."""
 import numpy as np
 import pytest
 import torch
@@ -26,8 +26,14 @@ WIDE = [(_shape(1024, 8, 1, ffn), n) for ffn in (8320, 16384, 16512, 20480, 2060
 # up to 16 rows, where a shape is wide enough: gate/up and QKV from 8 rows on, O and down from 13
 FEW = [(_shape(5120, 40, 8, 5376), n) for n in (10, 12, 13, 16)]
 
+# cuts along K: 2048 and 2176 (splits of 8 and 9 slices) around 33 and 64 rows; from 8 rows on with K = 8192, 4 splits of 16
+# columns and 8 of 32; 80 columns, and 160 with 8 splits; 192 columns (the widest tile)
+CUT = [(_shape(2048, 16, 2, 2176), n) for n in (32, 33, 64, 65, 128)] + \
+      [(_shape(1024, 8, 1, 8192), n) for n in (10, 16, 17, 64, 65, 127)] + \
+      [(_shape(5120, 40, 8, 8192), n) for n in (17, 64, 100)] + [(_shape(2048, 64, 16, 2176), n) for n in (40, 64)]
 
-@pytest.mark.parametrize("shape,n", NARROW + WIDE + FEW, ids=lambda v: str(v) if isinstance(v, int) else "h%d_f%d" % (v.hidden, v.ffn_dim))
+
+@pytest.mark.parametrize("shape,n", NARROW + WIDE + FEW + CUT, ids=lambda v: str(v) if isinstance(v, int) else "h%d_f%d" % (v.hidden, v.ffn_dim))
 def test_units_match_oracle(shape, n):
     pb = Problem(shape, [n - 9, 9], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)
     ctx = pb.context(max_tokens=n + 2)
