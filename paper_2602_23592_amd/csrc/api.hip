@@ -579,11 +579,13 @@ keep_status layer_back(keep_ctx* c, int layer, int n, const void* o_rows, const 
   EV(12);
   if (c->mfma) {
     auto B = [](const void* p) { return reinterpret_cast<const bf16_t*>(p); };
-    launch_gemm_mfma(B(o_rows), n, qd, bo, nullptr, d.hidden, EPI_RESIDUAL_STORE, B(x_in), c->x1, s, c->skinny_ws);
-    EV(6);
     const bool fuse_norm = gemm_fuses_norm(n, d.hidden, bg, d.ffn_dim, EPI_SWIGLU_STORE, c->skinny_ws != nullptr);
+    const bool normed = !fuse_norm && gemm_norms_output(n, qd, bo, d.hidden, c->skinny_ws != nullptr);
     const RowNorm norm{w.ln2, d.rms_eps};
-    if (!fuse_norm)
+    launch_gemm_mfma(B(o_rows), n, qd, bo, nullptr, d.hidden, EPI_RESIDUAL_STORE, B(x_in), c->x1, s, c->skinny_ws, nullptr,
+                     normed ? &norm : nullptr, normed ? c->hbuf : nullptr);
+    EV(6);
+    if (!fuse_norm && !normed)
       launch_rmsnorm<bf16_t>(B(c->x1), B(w.ln2), n, d.hidden, d.rms_eps, reinterpret_cast<bf16_t*>(c->hbuf), s);
     EV(7);
     launch_gemm_mfma(fuse_norm ? B(c->x1) : B(c->hbuf), n, d.hidden, bg, w.wup, d.ffn_dim, EPI_SWIGLU_STORE, nullptr,

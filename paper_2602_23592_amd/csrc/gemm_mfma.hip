@@ -1109,10 +1109,10 @@ bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool h
 
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws, const QkvEpilogue* qkv,
-                      const RowNorm* norm) {
+                      const RowNorm* norm, void* norm_out) {
   if (M <= 0 || N <= 0) return;
   if (gemm_stream_fits(M, K, B, N, epilogue, skinny_ws != nullptr)) {
-    launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, skinny_ws, qkv);
+    launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, skinny_ws, qkv, norm, norm_out);
     return;
   }
   if (skinny_ws && gemm_skinny_fits(M, K, B, N, epilogue)) {

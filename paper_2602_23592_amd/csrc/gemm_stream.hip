@@ -38,6 +38,9 @@ struct StreamArgs {
   void* C;
   float* part;  // cut along K: fp32 sums [splits][M][N]
   int splits;
+  const bf16_t* norm_w;  // k_stream_add_norm
+  float eps;
+  bf16_t* norm_out;
   QkvEpilogue qe;
 };
 
@@ -339,6 +342,57 @@ __global__ void __launch_bounds__(256) k_stream_add(StreamArgs g) {
   }
 }
 
+// The same with a residual and the RMSNorm of the finished rows behind it, a workgroup per row: one launch for two (64 rows of
+// 5120: 4.0 + 4.5 us before, 4.8 now).  The row's squares are added as k_rmsnorm adds them, so the outputs are the same.
+constexpr int ADD_THREADS = 1024;
+template <int S>
+__global__ void __launch_bounds__(ADD_THREADS) k_stream_add_norm(StreamArgs g) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];  // the row, rounded
+  __shared__ float s_red[4];
+  const int N = g.N, tid = threadIdx.x;
+  const size_t row = (size_t)blockIdx.x * N, step = (size_t)g.M * N;
+  for (int i = tid; i < N / 4; i += ADD_THREADS) {
+    f32x4 v[S];
+#pragma unroll
+    for (int z = 0; z < S; ++z) v[z] = *reinterpret_cast<const f32x4*>(g.part + z * step + row + i * 4);
+    const uint2 r = *reinterpret_cast<const uint2*>(g.residual + row + i * 4);
+#pragma unroll
+    for (int z = 1; z < S; ++z) v[0] += v[z];
+    uint2 o;
+    o.x = pack_bf16x2(bf16_bits_to_f32((uint16_t)(r.x & 0xffff)) + v[0][0], bf16_bits_to_f32((uint16_t)(r.x >> 16)) + v[0][1]);
+    o.y = pack_bf16x2(bf16_bits_to_f32((uint16_t)(r.y & 0xffff)) + v[0][2], bf16_bits_to_f32((uint16_t)(r.y >> 16)) + v[0][3]);
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(g.C) + row + i * 4) = o;
+    *reinterpret_cast<uint2*>(smem + i * 4) = o;
+  }
+  __syncthreads();
+  if (tid < 256) {
+    float ss = 0.f;
+    for (int i = tid; i < N / 8; i += 256) {
+      const uint4 u = *reinterpret_cast<const uint4*>(smem + i * 8);
+      const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = __uint_as_float(d[e] << 16), b = __uint_as_float(d[e] & 0xffff0000u);
+        ss += a * a;
+        ss += b * b;
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    if ((tid & 63) == 0) s_red[tid >> 6] = ss;
+  }
+  __syncthreads();
+  const float inv = 1.0f / sqrtf((s_red[0] + s_red[1] + s_red[2] + s_red[3]) / (float)N + g.eps);
+  for (int i = tid; i < N / 4; i += ADD_THREADS) {
+    const uint2 x = *reinterpret_cast<const uint2*>(smem + i * 4), w = *reinterpret_cast<const uint2*>(g.norm_w + i * 4);
+    auto n = [&](uint32_t a, uint32_t b) {
+      return pack_bf16x2(__uint_as_float(a << 16) * inv * __uint_as_float(b << 16),
+                         __uint_as_float(a & 0xffff0000u) * inv * __uint_as_float(b & 0xffff0000u));
+    };
+    *reinterpret_cast<uint2*>(g.norm_out + row + i * 4) = uint2{n(x.x, w.x), n(x.y, w.y)};
+  }
+}
+
 // columns of a workgroup where K is cut: a multiple of four
 int cut_columns(int N, int splits) { return ((N * splits + ST_WGS - 1) / ST_WGS + 3) / 4 * 4; }
 
@@ -383,6 +437,10 @@ void launch_stream_cut(const StreamArgs& g, int epilogue, hipStream_t s) {
   else if constexpr (MT <= 4)
     launch_stream_ring<EPI_STORE_F32, 14, MT, 1>(g, s);
   const int threads = g.M * (epilogue == EPI_QKV_ROPE ? g.N / 8 : g.N / 4);
+  if (g.norm_out) {
+    hipLaunchKernelGGL(g.splits == 8 ? k_stream_add_norm<8> : k_stream_add_norm<4>, dim3(g.M), dim3(ADD_THREADS), g.N * 2, s, g);
+    return;
+  }
   auto add = [&](void (*kern)(StreamArgs)) { hipLaunchKernelGGL(kern, dim3((threads + 255) / 256), dim3(256), 0, s, g); };
   if (epilogue == EPI_QKV_ROPE)
     add(g.splits == 8 ? k_stream_add<EPI_QKV_ROPE, 8> : k_stream_add<EPI_QKV_ROPE, 4>);
@@ -465,8 +523,13 @@ bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
   return B.n_parts == 1 && (epilogue == EPI_SWIGLU_STORE || epilogue == EPI_RESIDUAL_STORE);
 }
 
+bool gemm_norms_output(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws) {
+  return gemm_stream_fits(M, K, B, N, EPI_RESIDUAL_STORE, have_ws) && stream_splits(M, K, N, EPI_RESIDUAL_STORE, have_ws);
+}
+
 void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
-                        const bf16_t* residual, void* C, hipStream_t s, void* ws, const QkvEpilogue* qkv) {
+                        const bf16_t* residual, void* C, hipStream_t s, void* ws, const QkvEpilogue* qkv,
+                        const RowNorm* norm, void* norm_out) {
   StreamArgs g{};
   g.A = A;
   g.M = M;
@@ -488,6 +551,11 @@ void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, c
   g.splits = stream_splits(M, K, N, epilogue, ws != nullptr);
   if (g.splits) {
     g.part = reinterpret_cast<float*>(ws);
+    if (norm_out) {
+      g.norm_w = reinterpret_cast<const bf16_t*>(norm->w);
+      g.eps = norm->eps;
+      g.norm_out = reinterpret_cast<bf16_t*>(norm_out);
+    }
     if (M <= 32)
       launch_stream_cut<2>(g, epilogue, s);
     else if (M <= 64)

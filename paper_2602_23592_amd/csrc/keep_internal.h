@@ -192,7 +192,9 @@ void launch_score_finish(const float* rowmass, const int32_t* d_row_start, int32
 size_t gemm_ws_bytes();
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws = nullptr,
-                      const QkvEpilogue* qkv = nullptr, const RowNorm* norm = nullptr);
+                      const QkvEpilogue* qkv = nullptr, const RowNorm* norm = nullptr, void* norm_out = nullptr);
+// true where launch_gemm_mfma, with a norm and norm_out, also writes the RMSNorm of the rows that EPI_RESIDUAL_STORE finishes
+bool gemm_norms_output(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows that k_gemv holds in LDS)
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
 // true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows (k_gemv) and
@@ -209,7 +211,8 @@ void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, c
 // 8 to 128 rows of bf16 weights, all epilogues but the plain store; where it is the fastest
 bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
 void launch_gemm_stream(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
-                        const bf16_t* residual, void* C, hipStream_t s, void* ws, const QkvEpilogue* qkv);
+                        const bf16_t* residual, void* C, hipStream_t s, void* ws, const QkvEpilogue* qkv,
+                        const RowNorm* norm, void* norm_out);
 // h_row_start / h_set_off / m / instr_off: the host copy of the layer's row layout (as for
 // launch_build_rows), from which the work list is planned; h_stage: pinned host ints
 // (attn_mfma_stage_ints), d_scratch: device bytes (attn_mfma_scratch_bytes).
