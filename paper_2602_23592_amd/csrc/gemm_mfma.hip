@@ -1079,14 +1079,16 @@ static void launch_cfg(const bf16_t* A, int M, int K, const MfmaB& b, const bf16
 
 size_t gemm_ws_bytes() { return std::max(GEMM_SPLIT_WS_BYTES, gemm_skinny_ws_bytes()); }
 
-// 256x256 tiles (8 waves, 64x128 each) or 128x128 (4 waves, 32x128 each); a last, partly filled round of workgroups is
-// cut along K in either case.  The large tile moves half the operand bytes per flop but fills its last row of tiles
-// less and starts more slowly, so it needs work: tile K slices in all (`work`), rows that fill the tiles, or both.
-// Measured, large / small, in us (hidden 5120 and 3584, rows x K x columns):
-//   at least 10000: always large.  8000 with more than 128 rows: 160 x 3584 x 37888 87 / 90, 384 x 18944 x 3584 69 / 88,
-//   but 128 x 5120 x 27648 83 / 81.  4000 with tiles at least 0.8 full: 512 x 5120 x 7168 55 / 65, 256 x 13824 x 5120
-//   59 / 62, but 300 x 5120 x 7168 45 / 43.  3000 with more than 600 rows: 1024 x 5120 x 5120 65 / 96, 900 x 3584 x 4608
-//   47 / 57, but (2352) 768 x 3584 x 3584 41 / 39.
+// 256x256 tiles (k_gemm_256) or 128x128 (4 waves, 32x128 each); a last, partly filled round of workgroups is cut along K in
+// either case.  The large tile moves half the operand bytes per flop but fills its last row of tiles less and starts more
+// slowly, so it needs work: tile K slices in all (`work`), a long K, rows that fill the tiles, or rows at which the small
+// tiles need a second round.  Measured, small / large, in us (rows x K x columns):
+//   at least 8000 with more than 128 rows: 129 x 5120 x 27648 88 / 82, 512 rows 198 / 131; 129 x 3584 x 37888 87 / 82.
+//   4000 with K of at least 8192: 129 x 13824 x 5120 47.6 / 44.9, 192 rows 56.1 / 51.4; 129 x 18944 x 3584 45.5 / 43.8; but
+//   (2048) 512 x 8192 x 2048 36.7 / 42.9.  4000 with tiles at least 0.8 full: 448 x 5120 x 7168 58.9 / 52.8, but 320 rows
+//   45.3 / 46.8, and with a short K 512 x 2048 x 16384 45.9 / 52.2.
+//   3000 with more than 512 rows: 513 x 5120 x 5120 51.2 / 46.2, 513 x 5120 x 7168 80.3 / 63.2, 513 x 2048 x 16384 59.5 / 43.1,
+//   513 x 3584 x 4608 39.9 / 39.1; but (2352) 768 x 3584 x 3584 41.4 / 42.4, (1152) 513 x 2048 x 3072 23.2 / 30.5.
 static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
   int acc = 0;
   for (int p = 0; p < B.n_parts; ++p) {
@@ -1095,8 +1097,8 @@ static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
   }
   if (rows % 256 || K < 128) return false;  // (at least two K slices)
   const long tiles_m = (M + 255) / 256, work = tiles_m * (rows / 256) * (K / 64);
-  return work >= 10000 || (work >= 8000 && M > 128) || (work >= 4000 && M * 5L >= tiles_m * 256 * 4) ||
-         (work >= 3000 && M > 600);
+  return work >= 10000 || (work >= 8000 && M > 128) ||
+         (work >= 4000 && ((K >= 8192 && M > 128) || (K >= 3584 && M * 5L >= tiles_m * 256 * 4))) || (work >= 3000 && M > 512);
 }
 
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws) {
