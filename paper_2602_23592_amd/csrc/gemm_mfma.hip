@@ -5,7 +5,7 @@
 // sustains the higher rate under the chip's power limit: a register-only loop on random operands runs at
 // 2.03 PFLOP/s against 1.78 PFLOP/s for 32x32x16, and the whole kernel gains 4 %; operand bytes read from
 // LDS per flop are the same for both.)  A workgroup owns a
-// BM x BN tile of C; K is walked in 64-deep slices staged through LDS (two buffers, one
+// BM x BN tile of C (256 x 256: k_gemm_256, below, with an order of its own); K is walked in 64-deep slices staged through LDS (two buffers, one
 // barrier per slice, next slice streamed global -> LDS by global_load_lds_dwordx4 while the
 // current one is multiplied; operand fragments of the next step are read while a step multiplies).  LDS
 // rows are 128 B; their 16-byte chunks are XOR-swizzled by the row index so that the

@@ -2,7 +2,8 @@
 //
 // With so few rows the work is reading the weights once: these kernels are bound by HBM, not by the matrix cores.
 // They carry greedy decoding (one row), short instructions over a reused prompt and the caching of one short memory
-// unit (Section 4.1).  k_gemv (up to 16 rows, weights in bf16 or in the 4-bit form) finishes its outputs itself;
+// unit (Section 4.1).  k_gemv (up to 16 rows, weights in bf16 or in the 4-bit form; wide bf16 projections of 8 to 16 rows
+// are k_gemm_stream's) finishes its outputs itself;
 // k_gemm_skinny_w4 (17 to 48 rows, 4-bit form only) writes K slices that k_skinny_finish adds.
 #include <algorithm>
 
@@ -673,12 +674,10 @@ bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
       if (B.n_rows[p] % SK_BN) return false;
     if (epilogue == EPI_SWIGLU_STORE && N % SK_BN) return false;
   }
-  // Where streaming the weights stops paying, in us per layer of a unit cached on its own, all launches of a layer, at the
-  // 7B / 14B / 32B shapes.  k_gemv holds up to 16 rows in one MFMA tile and is no slower than what takes over at 17:
-  //   bf16, k_gemv against the matrix-core tiles: 2 rows 124 / 137 / 207 against 147 / 160 / 260, 8 rows 130 / 137 / 209
-  //   against 149 / 157 / 252, 16 rows 143 / 150 / 231 against 150 / 158 / 253.  Launch by launch with 16 rows at the 14B
-  //   shape: gate/up 54.9 against 57.6 + 4.7 (the pass that adds the cuts along K), output and down projection 25.0 against
-  //   21.7 + 4.4 on average, QKV 20.7 against 17.3 + 4.7.
+  // Where this kernel is the faster one, in us per layer of a unit cached on its own, all launches of a layer, at the
+  // 7B / 14B / 32B shapes.  k_gemv holds up to 16 rows in one MFMA tile:
+  //   bf16: what gemm_stream_fits leaves (the figures stand there).  Against the matrix-core tiles: 2 rows 124 / 137 / 207
+  //   against 147 / 160 / 260, 16 rows 143 / 150 / 231 against 150 / 158 / 253.
   //   4-bit, k_gemv against k_gemm_skinny_w4: 2 rows 78 / 81 / 113 against 86 / 96 / 120, 8 rows 81 / 84 / 116 against
   //   90 / 99 / 125, 16 rows 93 / 94 / 133 against 96 / 101 / 133.
   // k_gemm_skinny_w4 moves a quarter of the tiles' bytes and wins up to 48 rows (14B shape, 48 layers: 33 rows 6.9 ms

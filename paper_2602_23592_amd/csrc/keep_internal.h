@@ -187,8 +187,8 @@ void launch_score_finish(const float* rowmass, const int32_t* d_row_start, int32
                          hipStream_t s);
 
 // MFMA (bf16, head_dim 128) kernels
-// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernel for 17 to 48 rows on the 4-bit
-// form, and of the tiles that are cut along K to fill the last round of workgroups.  NULL: no weight streaming, no cuts.
+// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernels that cut K (8 to 128 rows, 17 to 48
+// on the 4-bit form), and of the tiles that are cut along K to fill the last round of workgroups.  NULL: no k_gemv, no cuts.
 size_t gemm_ws_bytes();
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws = nullptr,
@@ -197,8 +197,8 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
 bool gemm_norms_output(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows that k_gemv holds in LDS)
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
-// true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows (k_gemv) and
-// every launch on tiles.  That leaves 17 to 48 rows on the 4-bit form (k_gemm_skinny_w4), where the caller projects to
+// true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows (k_gemv),
+// 8 to 128 (k_gemm_stream) and every launch on tiles.  That leaves 17 to 48 rows on the 4-bit form (k_gemm_skinny_w4), where the caller projects to
 // fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel, as it does for the token-granularity scheme.
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // bf16 expansion of an INT4 matrix: out[rows, K] = bf16((code - zero) * scale)
