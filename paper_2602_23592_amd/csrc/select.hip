@@ -4,9 +4,12 @@
 // Every floating-point value that decides the selection is computed in binary32 in a fixed order (sums over
 // candidates in ascending order, one division each), so the result is a pure function of S.
 //
-// From 64 candidates on two kernels: k_row_totals (many workgroups: reading S once needs more than one CU) and k_select
-// (one workgroup: what is left is a chain of small steps that depend on each other).  Below, one wave does all of it
-// (k_select_small).
+// Fewer than 64 candidates: one wave does all of it (k_select_small).  From 64 on k_row_totals (many workgroups: reading S
+// once needs more than one CU) and k_select (one workgroup: what is left is a chain of small steps that depend on each
+// other).  From 900 on the first selections are k_select_step and k_propagate in turn (the propagation on many workgroups),
+// and k_select runs those that are left.
+#include <algorithm>
+
 #include "keep_internal.h"
 
 namespace keep {
@@ -203,16 +206,33 @@ __device__ int compact(const uint8_t* taken, int m, int32_t* list, int* s_cnt /*
   return n;
 }
 
+// What a selection that runs over several launches keeps between them, behind the m + 1 row totals
+struct SelectState {
+  int32_t* flags;  // [4]: selection ended, selections run, members of the set
+  uint64_t* key;   // [m] importances as sort keys
+  int32_t* list;   // [m] the set, ascending
+  uint8_t* rel;    // [m] its members
+};
+static SelectState select_state(float* scratch, int m) {
+  SelectState st;
+  int32_t* w = reinterpret_cast<int32_t*>(scratch) + (m + 1 + 1) / 2 * 2;
+  st.key = reinterpret_cast<uint64_t*>(w);
+  st.flags = w + 2 * m;
+  st.list = st.flags + 4;
+  st.rel = reinterpret_cast<uint8_t*>(st.list + m);
+  return st;
+}
+
 // The normalised score of (a, b) is S[a, b] / total_a with total_a the sum of row a in ascending order
 // (0 where the row is empty); it is formed where it is used, only the row totals are kept.
 //
 // Bound by its chain of small steps.  It reads only the rows of S that the propagation averages, 16 loads in flight per
-// thread.  1024 candidates, 308 kept, three selections: 118 us; one workgroup that also summed the rows, ranked every
-// candidate against every other and walked budget and output list one by one took 1020 us.
+// thread.  768 candidates, 115 kept, three selections: 72 us; 1024 candidates, 308 kept: 118 us (k_propagate's now).
 __global__ void __launch_bounds__(SEL_THREADS)
     k_select(const float* __restrict__ S, int m, int P, const int32_t* __restrict__ cand_len, int k_count,
              int token_budget, int mode, int hops, int set_only, const float* __restrict__ row_tot,
-             int32_t* __restrict__ out, const int32_t* __restrict__ cand_total, const int32_t* __restrict__ id_map) {
+             int32_t* __restrict__ out, const int32_t* __restrict__ cand_total, const int32_t* __restrict__ id_map,
+             int resume, SelectState st) {
   extern __shared__ __attribute__((aligned(16))) char sel_smem[];
   uint64_t* key = reinterpret_cast<uint64_t*>(sel_smem);  // [P]
   float* list_tot = reinterpret_cast<float*>(key + P);    // [m] row totals of the listed candidates
@@ -224,7 +244,7 @@ __global__ void __launch_bounds__(SEL_THREADS)
   // Callers that could not classify the budget on the host pass the candidates' token total: a budget that
   // takes every candidate or none is settled here without a selection (0 selections run), as the host does
   // for the other callers.
-  if (cand_total) {
+  if (cand_total && !resume) {
     const bool all = m > 0 && (mode == KEEP_BUDGET_GROUP_COUNT ? k_count >= m : token_budget >= *cand_total);
     const bool none = m == 0 || (mode == KEEP_BUDGET_GROUP_COUNT ? k_count == 0 : token_budget <= 0);
     if (all || none) {
@@ -237,13 +257,19 @@ __global__ void __launch_bounds__(SEL_THREADS)
       return;
     }
   }
+  if (resume && st.flags[0]) return;  // (the selection ended in the launches before)
 
   for (int b = threadIdx.x; b < m; b += SEL_THREADS) len[b] = cand_len[b];
   const float tq = row_tot[m];
-  for (int b = threadIdx.x; b < m; b += SEL_THREADS) key[b] = sel_key(tq > 0.f ? S[(size_t)m * m + b] / tq : 0.f, b);
-  take(key, m, P, len, k_count, token_budget, mode, rel);
+  if (resume) {
+    for (int b = threadIdx.x; b < m; b += SEL_THREADS) rel[b] = st.rel[b];
+    __syncthreads();
+  } else {
+    for (int b = threadIdx.x; b < m; b += SEL_THREADS) key[b] = sel_key(tq > 0.f ? S[(size_t)m * m + b] / tq : 0.f, b);
+    take(key, m, P, len, k_count, token_budget, mode, rel);
+  }
   int n_rel = compact(rel, m, list, s_cnt);
-  int runs = 1;
+  int runs = resume ? st.flags[1] : 1;
   const int max_runs = hops > 1 ? hops : 1;
   while (runs < max_runs) {
     for (int i = threadIdx.x; i < n_rel; i += SEL_THREADS) list_tot[i] = row_tot[list[i]];
@@ -297,29 +323,13 @@ __global__ void __launch_bounds__(SEL_THREADS)
 // The same selection over several launches, where there are enough candidates that the propagation, one division per
 // listed row and candidate, is worth more than one CU: k_select_step chooses and lists a set (one workgroup), and
 // k_propagate forms the next importances (a workgroup per 64 candidates).  A step that finds the set it was given ends
-// the selection: what is launched behind it returns at once.  Same sums, divisions and orders as in k_select.
+// the selection: what is launched behind it returns at once.  That still costs a launch, so only the first selections run
+// this way and k_select goes on from their state.  Same sums, divisions and orders as in k_select.
 //
 // k_propagate: lane = candidate.  Seven waves fetch the listed rows of a block of 112 and divide, the eighth adds the
 // block before in ascending order: its chain of additions, 8 cycles each, is what bounds the kernel.
 // ---------------------------------------------------------------------------------------------
 constexpr int PR_WAVES = 8, PR_ROWS = 16 * (PR_WAVES - 1);
-
-// scratch of the launches, behind the m + 1 row totals
-struct SelectState {
-  int32_t* flags;  // [4]: selection ended, selections run, members of the set
-  uint64_t* key;   // [m] importances as sort keys
-  int32_t* list;   // [m] the set, ascending
-  uint8_t* rel;    // [m] its members
-};
-static SelectState select_state(float* scratch, int m) {
-  SelectState st;
-  int32_t* w = reinterpret_cast<int32_t*>(scratch) + (m + 1 + 1) / 2 * 2;
-  st.key = reinterpret_cast<uint64_t*>(w);
-  st.flags = w + 2 * m;
-  st.list = st.flags + 4;
-  st.rel = reinterpret_cast<uint8_t*>(st.list + m);
-  return st;
-}
 
 __global__ void __launch_bounds__(PR_WAVES * 64)
     k_propagate(const float* __restrict__ S, int m, int set_only, const float* __restrict__ row_tot, SelectState st) {
@@ -520,8 +530,16 @@ size_t select_scratch_words(int32_t m) { return (size_t)(m + 1 + 1) / 2 * 2 + (s
 // From here on the propagation gets workgroups of its own.  Back to back, us for a call of two / three / three / four
 // selections that keep 5 / 10 / 15 / 40 % of the candidates: 512 candidates 31 / 53 / 54 / 110 in one workgroup against
 // 34 / 56 / 52 / 89, 768: 40 / 74 / 72 / 170 against 42 / 71 / 65 / 112, 1024: 44 / 87 / 90 / 236 against
-// 44 / 75 / 69 / 126, 4000: 202 / 581 / 741 / 2673 against 106 / 197 / 170 / 366.
+// 44 / 75 / 69 / 126, 4000: 202 / 581 / 741 / 2673 against 106 / 197 / 170 / 366.  (The line would lie lower for selections
+// that go on longer and keep more, but how many are made is not known at the launch, and two lose below it.)
 constexpr int SEL_SPREAD = 900;
+
+// How many selections run this way before k_select goes on from their state, so that a caller who asks for the fixed point
+// (any large `hops`) pays for few launches behind it.  Two empty launches cost 5 us.  A set that repeats at once, hops = 100,
+// us in one workgroup / with 8 / with 30 spread selections: 1024 candidates 47 / 77 / 221, 2048: 97 / 90 / 224, 4000: 270 / 128 / 238;
+// ten selections that keep 40 %: 638 / 391 / 317, 2164 / 884 / 511, 7658 / 2423 / 917.  With many candidates the empty launches
+// may therefore take as long as one workgroup's second selection would, which grows with their square.
+static int sel_spread_runs(int m) { return std::max(8, m * m / 450000); }
 
 void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t k_count, int32_t token_budget,
                    int32_t mode, int32_t hops, float* d_scratch, int32_t* d_out, hipStream_t s, bool set_only,
@@ -537,24 +555,25 @@ void launch_select(const float* S, int32_t m, const int32_t* d_cand_len, int32_t
   const int blocks = (m + 1 + RT_ROWS - 1) / RT_ROWS + (prep ? 1 : 0);
   hipLaunchKernelGGL(k_row_totals, dim3(blocks), dim3(RT_THREADS), 0, s, S, m, d_scratch, pr);
   const int max_runs = hops > 1 ? hops : 1;
-  if (max_runs > 1 && m >= SEL_SPREAD) {
-    const SelectState st = select_state(d_scratch, m);
+  const int spread = m >= SEL_SPREAD && max_runs > 1 ? std::min(max_runs, sel_spread_runs(m)) : 0;
+  const SelectState st = select_state(d_scratch, m);
+  if (spread) {
     const size_t sh = (size_t)P * 8 + (size_t)m * (2 * 4 + 1);
     static std::atomic<uint64_t> attr_done{0};
     set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select_step), 160 * 1024 - 256);
-    for (int run = 1; run <= max_runs; ++run) {
+    for (int run = 1; run <= spread; ++run) {
       if (run > 1)
         hipLaunchKernelGGL(k_propagate, dim3((m + 63) / 64), dim3(PR_WAVES * 64), 0, s, S, m, set_only ? 1 : 0, d_scratch, st);
       hipLaunchKernelGGL(k_select_step, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode,
                          run == 1 ? 1 : 0, d_scratch, st, d_out, pr.cand_total, pr.groups);
     }
-    return;
+    if (spread == max_runs) return;
   }
   const size_t sh = (size_t)P * 8 + (size_t)m * (3 * 4 + 2);  // <= 147 KB: m <= 6000
   static std::atomic<uint64_t> attr_done{0};
   set_max_dyn_smem_once(attr_done, reinterpret_cast<const void*>(k_select), 160 * 1024 - 256);
   hipLaunchKernelGGL(k_select, dim3(1), dim3(SEL_THREADS), sh, s, S, m, P, d_cand_len, k_count, token_budget, mode, hops,
-                     set_only ? 1 : 0, d_scratch, d_out, pr.cand_total, pr.groups);
+                     set_only ? 1 : 0, d_scratch, d_out, pr.cand_total, pr.groups, spread ? 1 : 0, st);
 }
 
 }  // namespace keep
