@@ -301,9 +301,13 @@ __device__ __forceinline__ f32x4 dots(const f32x4 (&a)[NT], const f32x4 (&b)[NT]
 // every eighth tile of 16 keys, and the waves' maxima, sums and outputs are joined through LDS in wave order
 // (reproducible).  Scores are formed transposed, S^T = K . Q^T, so that the lane owns a query row and its four
 // probabilities are, as they stand, the operand of O^T += V^T . P^T.  Operands come straight from the cache: a K row's
-// 64 bytes are one request of four lanes, and the next tile's K is requested before the present one is used.
+// 64 bytes are one request of four lanes, and the next tile's K is requested before the present one is used.  Of a V row a
+// lane reads four consecutive elements, one for each of four products: acc[4 g + u] holds in element e the output dimension
+// 64 g + 16 (lane / 16) + 4 e + u (what is left of the width in tiles of 16: 16 c + 4 (lane / 16) + e).
 // 2-layer, 4-head, 64-wide fp32 prefill of 1088 tokens (1088 and 320 rows): 24 us per layer on average against 84 with a
-// workgroup per (row, head) and a key per thread, which read the cache once per query row.  A cached value that is not
+// workgroup per (row, head) and a key per thread, which read the cache once per query row.  One row over 20 000 keys, two KV
+// heads of 256: 1.0 ms (4.5 ms with an element of V per load, each waited for in front of its product: a tile then costs as
+// many round trips as loads).  A cached value that is not
 // finite reaches the rows of its tile that do not see it (0 times infinity), as in the bf16 kernel.
 // ---------------------------------------------------------------------------
 constexpr int AG_WAVES = 8;
@@ -314,7 +318,7 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
                    const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_lo, int n_rows, int n_q_heads,
                    int n_kv_heads, T* __restrict__ o, float* __restrict__ lse) {
   constexpr int DH = NT * 16, LD = DH + 4;
-  constexpr bool AHEAD = NT <= 8;  // (wider heads leave no registers for a second tile)
+  constexpr bool AHEAD = NT <= 8;  // (wider heads leave no registers for a second tile, nor for K and V at once)
   extern __shared__ __attribute__((aligned(16))) float ag_smem[];  // [wave][16][LD]: outputs, then max and sum
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 15, kg = lane >> 4;
@@ -341,11 +345,26 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
   float m_run = -INFINITY, l_run = 0.f;
   for (int t = wave; t < n_tiles; t += AG_WAVES) {
     const int key0 = first + t * 16 + 4 * kg;  // the lane's four keys
-    if constexpr (AHEAD)
+    f32x4 v[4][(NT + 3) / 4];
+    auto load_v = [&]() {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const T* vr = vh + (size_t)min(key0 + e, last) * kv_dim;
+#pragma unroll
+        for (int g = 0; g < NT / 4; ++g) v[e][g] = ld4(vr + 64 * g + 4 * lq);
+#pragma unroll
+        for (int c = NT / 4 * 4; c < NT; ++c) v[e][c / 4][c % 4] = ldf(vr + 16 * c + lq);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // (the loads go out together, not each in front of its product)
+    };
+    if constexpr (AHEAD) {
+      load_v();
       load_head<NT>(k_row(min(t + AG_WAVES, n_tiles - 1)), kg, kn);
-    else
+    } else {
       load_head<NT>(k_row(t), kg, kf);
+    }
     f32x4 s = dots<NT>(kf, qf);
+    if constexpr (!AHEAD) load_v();
     float tmax = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -368,15 +387,11 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
     m_run = m_new;
 #pragma unroll
     for (int c = 0; c < NT; ++c) acc[c] *= alpha;
-    // acc[c]: output dimensions 16 c + 4 kg .. + 3 of the lane's query row
-    const T* vr[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) vr[e] = vh + (size_t)min(key0 + e, last) * kv_dim + lq;
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int c = 0; c < NT; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ldf(vr[e] + 16 * c), p[e], acc[c], 0, 0, 0);
+      for (int c = 0; c < NT; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e][c / 4][c % 4], p[e], acc[c], 0, 0, 0);
     if constexpr (AHEAD) {
 #pragma unroll
       for (int c = 0; c < NT; ++c) kf[c] = kn[c];
@@ -386,7 +401,13 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
   l_run += __shfl_xor(l_run, 32, 64);
   float* mine = ag_smem + (wave * 16 + lq) * LD;
 #pragma unroll
-  for (int c = 0; c < NT; ++c) *reinterpret_cast<f32x4*>(mine + 16 * c + 4 * kg) = acc[c];
+  for (int g = 0; g < NT / 4; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      *reinterpret_cast<f32x4*>(mine + 64 * g + 16 * kg + 4 * e) =
+          f32x4{acc[4 * g][e], acc[4 * g + 1][e], acc[4 * g + 2][e], acc[4 * g + 3][e]};
+#pragma unroll
+  for (int c = NT / 4 * 4; c < NT; ++c) *reinterpret_cast<f32x4*>(mine + 16 * c + 4 * kg) = acc[c];
   if (kg == 0) {
     mine[DH] = m_run;
     mine[DH + 1] = l_run;

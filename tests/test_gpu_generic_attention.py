@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dh,heads,kv,storage", [(16, 4, 4, "f32"), (32, 7, 1, "f32"), (48, 6, 2, "f32"), (80, 3, 3, "f32"),
-                                                 (96, 4, 2, "bf16"), (128, 5, 1, "f32"), (144, 2, 1, "f32"),
-                                                 (208, 3, 1, "bf16"), (256, 2, 2, "f32")])
+                                                 (96, 4, 2, "bf16"), (112, 2, 2, "f32"), (128, 5, 1, "f32"),
+                                                 (144, 2, 1, "f32"), (208, 3, 1, "bf16"), (224, 2, 1, "f32"),
+                                                 (256, 2, 2, "f32")])
 def test_layer(dh, heads, kv, storage):
     tol = 1e-4 if storage == "f32" else 2e-2
     shape = ks.ModelShape(1, 64, heads, kv, dh, 96, 97, 1.0e4, 1e-6, storage)
