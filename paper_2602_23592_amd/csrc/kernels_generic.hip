@@ -307,8 +307,7 @@ __device__ __forceinline__ f32x4 dots(const f32x4 (&a)[NT], const f32x4 (&b)[NT]
 // 2-layer, 4-head, 64-wide fp32 prefill of 1088 tokens (1088 and 320 rows): 24 us per layer on average against 84 with a
 // workgroup per (row, head) and a key per thread, which read the cache once per query row.  One row over 20 000 keys, two KV
 // heads of 256: 1.0 ms (4.5 ms with an element of V per load, each waited for in front of its product: a tile then costs as
-// many round trips as loads).  A cached value that is not
-// finite reaches the rows of its tile that do not see it (0 times infinity), as in the bf16 kernel.
+// many round trips as loads).
 // ---------------------------------------------------------------------------
 constexpr int AG_WAVES = 8;
 
@@ -326,11 +325,13 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
   const int x = min((int)blockIdx.x * 16 + lq, n_rows * rep - 1);  // this lane's query row (past the end: the last again)
   const int r = x / rep, head = hk * rep + x % rep;
   const int pos = row_pos[r], lo = row_lo ? row_lo[r] : 0;  // (lo: a unit cached on its own sees only itself)
-  int last = pos, first = lo;
+  int last = pos, first = lo, all_from = lo, all_to = pos;  // keys some row sees, keys every row sees
 #pragma unroll
   for (int off = 8; off > 0; off >>= 1) {
     last = max(last, __shfl_xor(last, off, 64));
     first = min(first, __shfl_xor(first, off, 64));
+    all_from = max(all_from, __shfl_xor(all_from, off, 64));
+    all_to = min(all_to, __shfl_xor(all_to, off, 64));
   }
   const int n_tiles = (last + 1 - first + 15) / 16;
   const float scale = 1.0f / sqrtf((float)DH);
@@ -387,11 +388,44 @@ __global__ void __launch_bounds__(AG_WAVES * 64)
     m_run = m_new;
 #pragma unroll
     for (int c = 0; c < NT; ++c) acc[c] *= alpha;
+    // A weight of zero does not hide an infinity or NaN from a row that does not see its key, so where rows differ in what
+    // they see such values stay out of the products and are added for the rows that see them.
+    const int tile0 = __builtin_amdgcn_readfirstlane(first + t * 16);
+    bool not_finite = false;
+    if (tile0 < __builtin_amdgcn_readfirstlane(all_from) || tile0 + 15 > __builtin_amdgcn_readfirstlane(all_to)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+          const float x = v[e][c / 4][c % 4];
+          const bool finite = fabsf(x) < INFINITY;
+          not_finite |= !finite;
+          v[e][c / 4][c % 4] = finite ? x : 0.f;
+        }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int c = 0; c < NT; ++c)
         acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e][c / 4][c % 4], p[e], acc[c], 0, 0, 0);
+    if (__any(not_finite)) {
+#pragma unroll 1
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float w = __shfl(p[e], g * 16 + lq, 64);
+          const int key = tile0 + 4 * g + e;
+          if (key < lo || key > pos) continue;
+          const T* vr = vh + (size_t)key * kv_dim;
+#pragma unroll
+          for (int c = 0; c < NT; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float x = ldf(vr + (c < NT / 4 * 4 ? c / 4 * 64 + 16 * kg + 4 * i + c % 4 : 16 * c + 4 * kg + i));
+              if (!(fabsf(x) < INFINITY)) acc[c][i] += w * x;
+            }
+        }
+    }
     if constexpr (AHEAD) {
 #pragma unroll
       for (int c = 0; c < NT; ++c) kf[c] = kn[c];
