@@ -516,45 +516,79 @@ void launch_attn_generic(const T* q, const T* k_cache, const T* v_cache, const i
 //   rowmass[t, j] = sum_h sum_{s in block j, s <= t} exp(q_t,h . k_s / sqrt(dh) - lse[t,h])
 // Rows and candidate keys are both in compact (prompt) order, so causality is s <= t.
 //
-// A wave owns 16 rows and one candidate block: per head it holds the rows' queries and walks the block's keys, 16 at a
-// time, with the dots of 16 rows in one product, where a lane per key read every query from LDS and its key row for
-// every row anew (1088 rows, 8 blocks, 4 heads of 64: 29 us against 77).
+// A product gives the dots of 16 rows with 16 keys.  Heads times key tiles of 16 rows and a candidate block are dealt out
+// evenly over the eight waves of a workgroup, in runs (a wave loads the rows' queries anew only where the head changes) with
+// the next tile's keys requested ahead; the waves' sums are added in wave order.  Rows that all lie in the block itself, or
+// in front of it, have nothing to do.  Bound by latency, hence the waves: 20 rows of an instruction towards one memory
+// of 1500 tokens, whose own rows are not counted, 16 heads of 128 in fp32, whole call: 367 us, 1467 with one wave per block.
+// Where many short blocks fill the chip, a wave takes a block alone (ALONE): see the launch.
 // ---------------------------------------------------------------------------
-template <typename T, int NT>
-__global__ void __launch_bounds__(256)
+constexpr int SG_WAVES = 8, SG_ALONE_WAVES = 4;
+
+template <typename T, int NT, bool ALONE>
+__global__ void __launch_bounds__((ALONE ? SG_ALONE_WAVES : SG_WAVES) * 64)
     k_score_rows_generic(const T* __restrict__ q, const T* __restrict__ k_compact, const float* __restrict__ lse,
                          const int32_t* __restrict__ row_start, int m, int n_rows, int n_q_heads, int n_kv_heads,
                          float* __restrict__ rowmass) {
   constexpr int DH = NT * 16;
+  __shared__ float s_sum[SG_WAVES][16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lq = lane & 15, kg = lane >> 4;
-  const int j = blockIdx.y * 4 + wave;
-  if (j >= m) return;
+  const int j = ALONE ? blockIdx.y * SG_ALONE_WAVES + wave : blockIdx.y, t0 = blockIdx.x * 16;
+  if (ALONE && j >= m) return;
   const int rep = n_q_heads / n_kv_heads, kv_dim = n_kv_heads * DH;
   const float scale = 1.0f / sqrtf((float)DH);
-  const int t = blockIdx.x * 16 + lq, tc = min(t, n_rows - 1);  // the lane's row
+  const int t = t0 + lq, tc = min(t, n_rows - 1);  // the lane's row
   const int s0 = row_start[j], s_end = row_start[j + 1];
+  const int t_end = min(t0 + 16, n_rows);
   const bool own = tc >= s0 && tc < s_end;  // a memory's attention to itself does not count
-  const int s1 = min(s_end, min((int)blockIdx.x * 16 + 16, n_rows));  // keys some row of the tile may see
-  const int seen = own ? s0 : min(s_end, tc + 1);                     // ... this row
+  const int s1 = t0 >= s0 && t_end <= s_end ? s0 : min(s_end, t_end);  // keys some row of the tile may see
+  const int seen = own ? s0 : min(s_end, tc + 1);                      // ... this row
   float sum = 0.f;
   if (s0 < s1) {
-    for (int h = 0; h < n_q_heads; ++h) {
-      f32x4 qf[NT], kf[NT];
-      load_head<NT>(q + ((size_t)tc * n_q_heads + h) * DH, kg, qf);
-      const float l = lse[(size_t)tc * n_q_heads + h];
-      const T* kh = k_compact + (h / rep) * DH;
-      for (int c0 = s0; c0 < s1; c0 += 16) {
-        load_head<NT>(kh + (size_t)min(c0 + lq, s1 - 1) * kv_dim, kg, kf);
-        const f32x4 d = dots<NT>(kf, qf);
+    const int tiles = (s1 - s0 + 15) / 16, items = n_q_heads * tiles;
+    int i = ALONE ? 0 : (int)((long)wave * items / SG_WAVES);
+    const int i_end = ALONE ? items : (int)((long)(wave + 1) * items / SG_WAVES);
+    int h = i / tiles, c = i - h * tiles, loaded = -1;
+    f32x4 qf[NT], kf[NT], kn[ALONE ? 1 : NT];
+    float l = 0.f;
+    auto keys = [&](f32x4 (&v)[NT]) {
+      load_head<NT>(k_compact + (size_t)min(s0 + 16 * c + lq, s1 - 1) * kv_dim + (h / rep) * DH, kg, v);
+    };
+    if (!ALONE && i < i_end) keys(kf);
+    for (; i < i_end; ++i) {
+      const int key0 = s0 + 16 * c + 4 * kg;  // the lane's four keys
+      if (h != loaded) {
+        load_head<NT>(q + ((size_t)tc * n_q_heads + h) * DH, kg, qf);
+        l = lse[(size_t)tc * n_q_heads + h];
+        loaded = h;
+      }
+      if constexpr (ALONE) keys(kf);
+      if (++c == tiles) c = 0, ++h;
+      if constexpr (!ALONE) {
+        if (i + 1 < i_end) keys(kn);
+      }
+      const f32x4 d = dots<NT>(kf, qf);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum += c0 + 4 * kg + e < seen ? expf(d[e] * scale - l) : 0.f;
+      for (int e = 0; e < 4; ++e) sum += key0 + e < seen ? expf(d[e] * scale - l) : 0.f;
+      if constexpr (!ALONE) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u) kf[u] = kn[u];
+      }
+    }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if constexpr (!ALONE) {
+      if (kg == 0) s_sum[wave][lq] = sum;
+      __syncthreads();
+      if (wave == 0) {
+        sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < SG_WAVES; ++w) sum += s_sum[w][lq];
       }
     }
   }
-  sum += __shfl_xor(sum, 16, 64);
-  sum += __shfl_xor(sum, 32, 64);
-  if (kg == 0 && t < n_rows) rowmass[(size_t)t * m + j] = sum;
+  if ((ALONE || wave == 0) && kg == 0 && t < n_rows) rowmass[(size_t)t * m + j] = sum;
 }
 
 template <typename T>
@@ -562,9 +596,18 @@ void launch_score_rows_generic(const T* q, const T* k_compact, const float* lse,
                                int32_t n_rows, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                                float* rowmass, hipStream_t s) {
   if (n_rows <= 0 || m <= 0) return;
+  // Many short blocks fill the chip with one wave each, and eight waves that find little to do cost more than they save.
+  // 4000 rows, 250 blocks of 16 tokens, whole call in us, one wave / eight: 8 heads of 256 1019 / 1276, 6 heads of 48
+  // 185 / 210; from 32 heads times key tiles on the same (32 heads of 64: equal).
+  const long pairs = (long)((n_rows + 15) / 16) * m;
+  const bool alone = pairs >= 4096 && (long)n_q_heads * ((n_rows / m + 15) / 16) < 32;
+  auto launch = [&](auto kern, int blocks_y, int waves) {
+    hipLaunchKernelGGL(kern, dim3((n_rows + 15) / 16, blocks_y), dim3(waves * 64), 0, s, q, k_compact, lse, d_row_start, m,
+                       n_rows, n_q_heads, n_kv_heads, rowmass);
+  };
 #define GO(NT)                                                                                                        \
-  hipLaunchKernelGGL((k_score_rows_generic<T, NT>), dim3((n_rows + 15) / 16, (m + 3) / 4), dim3(256), 0, s, q, k_compact, \
-                     lse, d_row_start, m, n_rows, n_q_heads, n_kv_heads, rowmass)
+  alone ? launch(k_score_rows_generic<T, NT, true>, (m + SG_ALONE_WAVES - 1) / SG_ALONE_WAVES, SG_ALONE_WAVES)        \
+        : launch(k_score_rows_generic<T, NT, false>, m, SG_WAVES)
   FOR_HEAD_TILES(head_dim / 16, GO)
 #undef GO
 }

@@ -39,6 +39,25 @@ def test_layer(dh, heads, kv, storage):
             assert np.abs(S - S_ref).max() <= tol * S_ref.max()
 
 
+@pytest.mark.parametrize("glen,lq,heads", [([70, 1], 20, 4), ([33], 1, 7), ([4] * 256, 5, 3), ([5, 2] * 120, 40, 6)],
+                         ids=["long", "one", "short", "ragged"])
+def test_scores(glen, lq, heads):
+    """Few long memories, whose rows mostly lie in the block they would look at, and so many short ones that a block is one
+    wave's (4096 pairs of 16 rows and a block)."""
+    shape = ks.ModelShape(1, 64, heads, 1, 32, 96, 97, 1.0e4, 1e-6, "f32")
+    pb = Problem(shape, glen, lq, seed=lq, std=0.1, bias=True, random_cache=True)
+    ctx, pr = pb.context(), pb.prompt()
+    for groups in (list(range(len(glen))), [0], list(range(0, len(glen), 2))):
+        n_rows = pr.n_rows(groups)
+        x_t = ks.make_random_rows(n_rows, shape.hidden, "f32", seed=len(groups))
+        kh, vh = pb.oracle_joined_cache(0)
+        _, _, want = ko.selective_layer(pb.sh, pb.layers[0], ks.to_numpy_f64(x_t), groups, glen, lq, kh, vh)
+        kc, vc = pb.empty_cache(1)
+        ctx.recompute_layer(pr, 0, groups, x_t.cuda(), torch.empty_like(x_t, device="cuda"), kc[0], vc[0])
+        _, _, S = ctx.score_groups(pr, 0, groups, 0.5, 2)
+        assert np.abs(S - want).max() <= 1e-4 * want.max()
+
+
 @pytest.mark.parametrize("dh,storage", [(16, "f32"), (96, "bf16"), (112, "f32"), (256, "f32")])
 def test_values_that_are_not_finite_reach_the_rows_that_see_them(dh, storage):
     """Rows of two memories and the instruction share a tile of 16 query rows; the memory between them, which is not
