@@ -1113,7 +1113,7 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
                       const bf16_t* residual, void* C, hipStream_t s, void* skinny_ws, const QkvEpilogue* qkv,
                       const RowNorm* norm, void* norm_out) {
   if (M <= 0 || N <= 0) return;
-  if (gemm_stream_fits(M, K, B, N, epilogue, skinny_ws != nullptr)) {
+  if (gemm_stream_fits(M, K, B, N, epilogue, skinny_ws != nullptr) && aligned16(B2)) {
     launch_gemm_stream(A, M, K, B, B2, N, epilogue, residual, C, s, skinny_ws, qkv, norm, norm_out);
     return;
   }
@@ -1133,7 +1133,8 @@ void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, con
   const bf16_t* b2 = reinterpret_cast<const bf16_t*>(B2);
   const int rows = epilogue == EPI_SWIGLU_STORE ? 2 * N : N;
   const QkvEpilogue qe = qkv ? *qkv : QkvEpilogue{};
-  if (big_tiles(M, K, B, rows))
+  // (k_gemm_256 also loads the residual straight to LDS)
+  if (big_tiles(M, K, B, rows) && parts_aligned16(B) && aligned16(B2) && aligned16(residual))
     launch_cfg<256, 256, 2, 2, 64, 2>(A, M, K, b, b2, N, epilogue, residual, C, s, skinny_ws, qe);
   else if (rows % 128 == 0)
     // (a wave as wide as the tile: a head per wave for the fused QKV epilogue, and where weights bound the launch the

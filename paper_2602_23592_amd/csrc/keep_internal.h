@@ -121,6 +121,14 @@ struct GemmB {
   const void* w4_scale_zero_b2;
 };
 
+// Loads that go straight to LDS are only made from addresses that are multiples of their 16 bytes.
+inline bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+inline bool parts_aligned16(const GemmB& B) {
+  for (int p = 0; p < B.n_parts; ++p)
+    if (!aligned16(B.ptr[p])) return false;
+  return true;
+}
+
 // ---------------------------------------------------------------------------
 // launchers (every one validates nothing: api.hip checks shapes first)
 // ---------------------------------------------------------------------------

@@ -21,6 +21,8 @@ WIDE = ks.ModelShape(2, 8256, 2, 1, 128, 320, 211, 1.0e6, 1e-6, "bf16")
 # blocks) and more than one of them, and so many heads that a QKV tile holds 16 column pairs; and the same for the output
 # and down projections
 FAN = ks.ModelShape(2, 512, 28, 4, 128, 8320, 211, 1.0e6, 1e-6, "bf16")
+# wide enough for the ring of stages from 8 rows on, which takes no weights at odd addresses
+RING = ks.ModelShape(2, 5120, 40, 8, 128, 5376, 211, 1.0e6, 1e-6, "bf16")
 WIDE4 = ks.ModelShape(2, 8320, 2, 1, 128, 384, 211, 1.0e6, 1e-6, "bf16")
 
 
@@ -30,7 +32,7 @@ def _odd(t):
 
 
 @pytest.mark.parametrize("shape,n,aligned", [(s, n, True) for s in (NARROW, WIDE) for n in (1, 2, 15, 16, 17)] +
-                         [(FAN, n, True) for n in (1, 2, 9, 16)] + [(FAN, n, False) for n in (1, 9)],
+                         [(FAN, n, True) for n in (1, 2, 9, 16)] + [(FAN, n, False) for n in (1, 9)] + [(RING, n, False) for n in (10, 16)],
                          ids=lambda v: "h%d" % v.hidden if isinstance(v, ks.ModelShape) else str(v))
 def test_few_rows_match_oracle(shape, n, aligned):
     pb = Problem(shape, [n], 1, seed=n, std=0.5 / np.sqrt(shape.hidden), bias=True)

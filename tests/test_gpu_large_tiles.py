@@ -48,3 +48,20 @@ def test_units_in_one_pass_match_single_units(problem, n):
             ev = max_rel(to_np(vc[l, first:first + count]), to_np(v1[l]))
             print(n, "layer", l, "rows", first, count, "K %.2e V %.2e" % (ek, ev))
             assert ek < 2e-2 and ev < 2e-2
+
+
+def test_hidden_rows_at_an_odd_address():
+    """The residual of the output projection at an address that is no multiple of 4 bytes (3000 rows: large tiles otherwise)."""
+    pb = Problem(ks.ModelShape(1, 2048, 16, 2, 128, 1024, 211, 1.0e6, 1e-6, "bf16"), [2950], 50, std=0.5 / np.sqrt(2048),
+                 random_cache=True)
+    ctx, pr = pb.context(), pb.prompt()
+    x = torch.randn((3000, 2048), generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).cuda()
+    odd = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape).copy_(x)
+    outs = []
+    for rows in (x, odd):
+        out = torch.empty_like(x)
+        kc, vc = pb.empty_cache()
+        ctx.recompute_layer(pr, 0, [0], rows, out, kc[0], vc[0])
+        torch.cuda.synchronize()
+        outs.append(to_np(out) - to_np(x))
+    assert np.isfinite(outs[0]).all() and max_rel(outs[1], outs[0]) < 2e-2
