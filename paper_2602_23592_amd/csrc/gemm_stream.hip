@@ -49,8 +49,10 @@ __device__ __forceinline__ constexpr int st_vmcnt(int n) { return 0x0F70 | (n & 
 // element offset of 16-byte chunk `chunk` of row `row` in a [rows][64] tile: 16 consecutive rows cover all banks
 __device__ __forceinline__ int st_off(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3); }
 
+// (One workgroup per CU: the ring leaves no LDS for another.  The widest tiles need more than half of the registers; for the
+// narrower ones the bound keeps the accumulators in vector registers.)
 template <int EPI, int UT, int MT, int SUB, int ST>
-__global__ void __launch_bounds__(256, 2) k_gemm_stream(StreamArgs g) {
+__global__ void __launch_bounds__(256, UT >= 14 ? 1 : 2) k_gemm_stream(StreamArgs g) {
   constexpr bool PAIRS = EPI == EPI_SWIGLU_STORE || EPI == EPI_QKV_ROPE;
   constexpr bool CUT = EPI == EPI_STORE_F32;       // one of the splits along K, one tile: fp32 sums for k_stream_add
   constexpr int UH = PAIRS ? UT / 2 : UT;          // weight tiles of 16 units
@@ -496,7 +498,8 @@ bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
   if (!parts_aligned16(B)) return false;
   // Up to 16 rows k_gemv streams as well, with every wave's activations from L2 beside its weights, us, k_gemv / this kernel:
   //   gate/up 5120 x 27648: 4 rows 49.8 / 50.4, 8 rows 51.1 / 50.5, 16 rows 54.2 / 50.6; 3584 x 37888: 8 rows 49.8 / 48.3,
-  //   16 rows 53.9 / 48.3; but 5120 x 55296: 13 rows 103.6 / 104.9, 16 rows 108.0 / 105.5.
+  //   16 rows 53.9 / 48.3; wider ones stay with k_gemv: 8192 x 57344, 8 rows 160 / 192, 16 rows 165 / 192 (though at 5120 x 55296
+  //   this kernel would win: 8 rows 99.2 / 96.8, 16 rows 108.0 / 97.2).
   //   QKV at 5120: 4 rows 16.0 / 15.5, 8 rows 17.0 / 15.6, 16 rows 18.9 / 16.2; at 3584: 8 rows 12.2 / 11.6, 16 rows 13.5 /
   //   11.8; but at 2048, 16 rows: 7.7 / 8.3.
   //   O at 5120: 12 rows 13.5 / 13.7, 16 rows 14.4 / 13.9; but 3584 x 3584, 13 rows: 10.1 / 10.2.
@@ -508,7 +511,7 @@ bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
   } else if (!cut && epilogue != EPI_SWIGLU_STORE && (K > 5120 || M > (K <= 4096 ? 64 : 48))) {
     // Tiles of 128x128 cut along K / this kernel without cuts, us:
     //   gate/up 5120 x 27648, 64 rows 70.8 / 57.0, 128 rows 81.1 / 72.6; 3584 x 37888 68.3 / 51.6, 80.9 / 64.5; 5120 x 55296,
-    //   64 rows 131 / 112; 2048 x 16384 22.3 / 17.5, 28.9 / 21.0: always here.
+    //   64 rows 131 / 102; 2048 x 16384 22.3 / 17.5, 28.9 / 21.0: always here.
     //   O and QKV at 5120: 32 rows 16.6 / 14.8 and 20.1 / 18.0, 48 rows 19.6 / 18.1 and 22.3 / 21.2, 64 rows 20.2 / 19.9 and
     //   23.2 / 24.4; at 3584, 64 rows: 16.7 / 13.7 and 17.2 / 15.6, 80 rows: 17.9 / 18.7 and 20.2 / 21.9; at 2048, 64 rows:
     //   11.8 / 8.7 and 13.3 / 10.7.
