@@ -452,12 +452,12 @@ void launch_stream_cut(const StreamArgs& g, int epilogue, hipStream_t s) {
 
 template <int MT>
 void launch_stream_rows(const StreamArgs& g, int epilogue, hipStream_t s) {
+  if constexpr (MT <= 4) {  // (with more rows QKV and O are cut along K, or not here)
+    if (epilogue == EPI_QKV_ROPE) return launch_stream_ring<EPI_QKV_ROPE, 2, MT, 2>(g, s);
+    if (epilogue == EPI_RESIDUAL_STORE) return launch_stream_ring<EPI_RESIDUAL_STORE, 2, MT, 2>(g, s);
+  }
   const int pairs = (g.N + ST_WGS - 1) / ST_WGS;  // gate/up: of a workgroup, if it takes one tile
-  if (epilogue == EPI_QKV_ROPE)
-    launch_stream_ring<EPI_QKV_ROPE, 2, MT, 2>(g, s);
-  else if (epilogue == EPI_RESIDUAL_STORE)
-    launch_stream_ring<EPI_RESIDUAL_STORE, 2, MT, 2>(g, s);
-  else if (pairs <= 32)
+  if (pairs <= 32)
     launch_stream_ring<EPI_SWIGLU_STORE, 4, MT, 1>(g, s);
   else if (pairs <= 64)
     launch_stream_ring<EPI_SWIGLU_STORE, 8, MT, 1>(g, s);
