@@ -8,7 +8,13 @@
 // per stage, so that 70 to 140 KB per CU are on their way: tiles of 128x128 with two stages had half of that, on 0.6 to
 // 0.85 of the chip, and each launch a second one behind it.  The weights are the A operand of v_mfma_f32_16x16x32_bf16,
 // 16 columns per tile, the activations the B operand, 16 rows per tile; a wave owns one or two of the activation tiles.
-// The loads run on over the ends of a workgroup's tiles.  (Workgroups that start at different places along K: no change.)
+// The loads run on over the ends of a workgroup's tiles.
+//
+// Where the weight rows are a multiple of 4 KB apart, workgroups that walk K side by side ask the same memory channels at the
+// same time, so they start at different slices and go round (us, side by side / spread; k_gemv or tiles before them): gate/up
+// 4096 x 28672, 8 rows 43.3: 46.1 / 41.3, 64 rows 56.1: 47.7 / 42.7; 4096 x 22016, 8 rows 34.2: 37.4 / 33.1; 4096 x 49152, 64
+// rows 100.6: 85.1 / 72.3; down 16384 x 6144, 8 rows 41.8: 48.4 / 37.2, 64 rows 47.4: 52.3 / 39.8; QKV 8192 x 10240, 64 rows
+// 40.0: 47.0 / 35.7.  Other distances, O, and cuts of at most 64 columns a workgroup lose 1 to 3 % and start side by side.
 //
 // Where the activations of the whole of K would cost a CU more than its few columns of weights (down projections, O and QKV
 // from 17 or 33 rows on), K is cut in 4 or 8: a workgroup then has 4 or 8 times the columns of one split, writes fp32 sums,
@@ -105,15 +111,18 @@ __global__ void __launch_bounds__(256, UT >= 14 ? 1 : 2) k_gemm_stream(StreamArg
       src[i] = row + c * 8 + (size_t)it0 * SUB * 64;
     }
   };
-  int lt = 0, li = 0, slot = 0;  // tile, stage of the tile and place in the ring of the next stage to request
+  int lt = 0, li = 0, slot = 0;  // tile, stages of it requested and place in the ring of the next stage to request
+  const bool apart = K % 2048 == 0 && (CUT ? g.units > 64 : PAIRS);
+  int at = !apart ? 0 : (CUT ? wg * 3 % n_it : wg * n_it / ST_WGS);  // stage along K
   auto request = [&]() {
 #pragma unroll
     for (int sub = 0; sub < SUB; ++sub)
 #pragma unroll
       for (int i = 0; i < LPS; ++i)
-        __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + ((size_t)li * SUB + sub) * 64),
+        __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + ((size_t)at * SUB + sub) * 64),
                                          (lptr_t)(smem + slot * STAGE + sub * SLICE + (wave * LPS + i) * 512), 16, 0, 0);
     slot = slot + 1 == ST ? 0 : slot + 1;
+    at = at + 1 == n_it ? 0 : at + 1;
     if (++li == n_it) {
       li = 0;
       if (++lt < n_tiles) aim(wg + lt * gridDim.x);
