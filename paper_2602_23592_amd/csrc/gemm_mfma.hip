@@ -1084,11 +1084,12 @@ size_t gemm_ws_bytes() { return std::max(GEMM_SPLIT_WS_BYTES, gemm_skinny_ws_byt
 // slowly, so it needs work: tile K slices in all (`work`), a long K, rows that fill the tiles, or rows at which the small
 // tiles need a second round.  Measured, small / large, in us (rows x K x columns):
 //   at least 8000 with more than 128 rows: 129 x 5120 x 27648 88 / 82, 512 rows 198 / 131; 129 x 3584 x 37888 87 / 82.
-//   4000 with K of at least 8192: 129 x 13824 x 5120 47.6 / 44.9, 192 rows 56.1 / 51.4; 129 x 18944 x 3584 45.5 / 43.8; but
-//   (2048) 512 x 8192 x 2048 36.7 / 42.9.  4000 with tiles at least 0.8 full: 448 x 5120 x 7168 58.9 / 52.8, but 320 rows
+//   4000 with K of at least 8192 and 3072 columns: 129 x 13824 x 5120 47.6 / 44.9, 192 rows 56.1 / 51.4; 129 x 18944 x 3584
+//   45.5 / 43.8; but 300 x 16384 x 2048 41.4 / 43.3, (2048) 512 x 8192 x 2048 36.7 / 42.9.  4000 with tiles at least 0.8 full: 448 x 5120 x 7168 58.9 / 52.8, but 320 rows
 //   45.3 / 46.8, and with a short K 512 x 2048 x 16384 45.9 / 52.2.
-//   3000 with more than 512 rows: 513 x 5120 x 5120 51.2 / 46.2, 513 x 5120 x 7168 80.3 / 63.2, 513 x 2048 x 16384 59.5 / 43.1,
-//   513 x 3584 x 4608 39.9 / 39.1; but (2352) 768 x 3584 x 3584 41.4 / 42.4, (1152) 513 x 2048 x 3072 23.2 / 30.5.
+//   3200 with more than 512 rows: 513 x 5120 x 5120 51.2 / 46.2, 513 x 5120 x 7168 80.3 / 63.2, 513 x 2048 x 16384 59.5 / 43.1,
+//   513 x 6912 x 2560 39.3 / 39.2; but (3072) 513 x 4096 x 4096 34.7 / 36.9.  3000 with more than 600: 700 x 4096 x 4096 43.6 /
+//   42.0; but (2352) 768 x 3584 x 3584 41.4 / 42.4, (1152) 513 x 2048 x 3072 23.2 / 30.5.
 static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
   int acc = 0;
   for (int p = 0; p < B.n_parts; ++p) {
@@ -1098,7 +1099,8 @@ static bool big_tiles(int32_t M, int32_t K, const GemmB& B, int32_t rows) {
   if (rows % 256 || K < 128) return false;  // (at least two K slices)
   const long tiles_m = (M + 255) / 256, work = tiles_m * (rows / 256) * (K / 64);
   return work >= 10000 || (work >= 8000 && M > 128) ||
-         (work >= 4000 && ((K >= 8192 && M > 128) || (K >= 3584 && M * 5L >= tiles_m * 256 * 4))) || (work >= 3000 && M > 512);
+         (work >= 4000 && ((K >= 8192 && rows >= 3072 && M > 128) || (K >= 3584 && M * 5L >= tiles_m * 256 * 4))) ||
+         (work >= 3200 && M > 512) || (work >= 3000 && M > 600);
 }
 
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws) {
