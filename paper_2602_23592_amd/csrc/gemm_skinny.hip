@@ -4,7 +4,7 @@
 // They carry greedy decoding (one row), short instructions over a reused prompt and the caching of one short memory
 // unit (Section 4.1).  k_gemv (up to 16 rows, weights in bf16 or in the 4-bit form; wide bf16 projections of 8 to 16 rows
 // are k_gemm_stream's) finishes its outputs itself;
-// k_gemm_skinny_w4 (17 to 48 rows, 4-bit form only) writes K slices that k_skinny_finish adds.
+// k_gemm_skinny_w4 (17 to 32 or 40 rows, 4-bit form only) writes K slices that k_skinny_finish adds.
 #include <algorithm>
 
 #include "keep_internal.h"
@@ -531,7 +531,7 @@ struct SkinnyW4 {
   int32_t begin[4];  // first output column of each part; unused parts never match
 };
 
-// 17 to 48 rows on the 4-bit form.  A workgroup owns 64 weight rows (output columns) and one of S slices of K; its
+// 17 to 40 rows on the 4-bit form.  A workgroup owns 64 weight rows (output columns) and one of S slices of K; its
 // four waves take the slice's steps round-robin, add their tiles through LDS and write fp32 partials [S][M][ld].
 // (Letting the workgroup that finishes a column tile last add the slices, found by a ticket counter, was measured
 // and dropped: the device-wide release each workgroup then needs writes back the XCD's L2.)  A wave step covers one
@@ -680,10 +680,9 @@ bool gemm_skinny_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilo
   //   against 147 / 160 / 260, 16 rows 143 / 150 / 231 against 150 / 158 / 253.
   //   4-bit, k_gemv against k_gemm_skinny_w4: 2 rows 78 / 81 / 113 against 86 / 96 / 120, 8 rows 81 / 84 / 116 against
   //   90 / 99 / 125, 16 rows 93 / 94 / 133 against 96 / 101 / 133.
-  // k_gemm_skinny_w4 moves a quarter of the tiles' bytes and wins up to 48 rows (14B shape, 48 layers: 33 rows 6.9 ms
-  // against 7.8 with bf16 weights, 48 rows 8.1 against 8.2).
+  // k_gemm_skinny_w4 goes on from there as far as the 4-bit form is read.
   if (gemv_fits(M, K, B)) return true;
-  return B.has_w4 && M > GV_MAX_ROWS && M <= 48 && epilogue != EPI_QKV_ROPE && (size_t)M * (size_t)ld <= SK_MAX_PART_FLOATS;
+  return reads_w4(B, M, K, N) && M > GV_MAX_ROWS && epilogue != EPI_QKV_ROPE && (size_t)M * (size_t)ld <= SK_MAX_PART_FLOATS;
 }
 
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws) {
@@ -727,7 +726,7 @@ void launch_gemm_skinny(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, c
       one_row ? launch_gemv_rows<true, false>(g, epilogue, s) : launch_gemv_rows<false, false>(g, epilogue, s);
     return;
   }
-  // 17 to 48 rows, 4-bit form
+  // 17 to 40 rows, 4-bit form
   SkinnyW4 q{};
   for (int p = 0; p < B.n_parts; ++p) {
     q.codes[p] = reinterpret_cast<const uint8_t*>(B.w4_codes[p]);

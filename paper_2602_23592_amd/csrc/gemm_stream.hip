@@ -503,7 +503,7 @@ int stream_splits(int M, int K, int N, int epilogue, bool have_ws) {
 
 bool gemm_stream_fits(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws) {
   if (M > ST_MAX_ROWS || K % 128 || K < 1024) return false;  // (stages of two slices; at least eight of them)
-  if (B.has_w4 && M <= 48) return false;                     // (the 4-bit form is read)
+  if (reads_w4(B, M, K, N)) return false;
   if (!parts_aligned16(B)) return false;
   // Up to 16 rows k_gemv streams as well, with every wave's activations from L2 beside its weights, us, k_gemv / this kernel:
   //   gate/up 5120 x 27648: 4 rows 49.8 / 50.4, 8 rows 51.1 / 50.5, 16 rows 54.2 / 50.6; 3584 x 37888: 8 rows 49.8 / 48.3,

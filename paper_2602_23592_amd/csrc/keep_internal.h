@@ -113,13 +113,21 @@ struct GemmB {
   int32_t n_rows[3];
   int32_t n_parts;
   // INT4 form of the same parts (codes, scale/zero words) and of the second operand of the SwiGLU
-  // epilogue; read instead of `ptr` by the launches that stream the weights (at most 48 rows)
+  // epilogue; read instead of `ptr` by the launches of few rows (reads_w4)
   bool has_w4;
   const void* w4_codes[3];
   const void* w4_scale_zero[3];
   const void* w4_codes_b2;
   const void* w4_scale_zero_b2;
 };
+
+// Rows up to which a launch reads the 4-bit form where there is one, and not its bf16 expansion.  A unit of four layers at the
+// 14B and 7B shapes, three at the 32B one, two at hidden 8192, us, 4-bit form / bf16 weights: 32 rows 425 / 478, 376 / 430, 394 / 473;
+// 33 rows 510 / 485, 467 / 443, 499 / 498, 383 / 415; 40 rows 545 / 492, 479 / 448, 524 / 498, 407 / 418; 48 rows 588 / 506,
+// 520 / 463, 571 / 510, 445 / 421.
+inline bool reads_w4(const GemmB& B, int32_t M, int32_t K, int32_t N) {
+  return B.has_w4 && M <= (K >= 8192 && N >= 8192 ? 40 : 32);
+}
 
 // Loads that go straight to LDS are only made from addresses that are multiples of their 16 bytes.
 inline bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
@@ -195,7 +203,7 @@ void launch_score_finish(const float* rowmass, const int32_t* d_row_start, int32
                          hipStream_t s);
 
 // MFMA (bf16, head_dim 128) kernels
-// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernels that cut K (8 to 128 rows, 17 to 48
+// skinny_ws: device scratch of gemm_ws_bytes(): partials of the weight-streaming kernels that cut K (8 to 128 rows, 17 to 40
 // on the 4-bit form), and of the tiles that are cut along K to fill the last round of workgroups.  NULL: no k_gemv, no cuts.
 size_t gemm_ws_bytes();
 void launch_gemm_mfma(const bf16_t* A, int32_t M, int32_t K, const GemmB& B, const void* B2, int32_t N, int epilogue,
@@ -206,8 +214,8 @@ bool gemm_norms_output(int32_t M, int32_t K, const GemmB& B, int32_t N, bool hav
 // true where launch_gemm_mfma takes the un-normalised row with a RowNorm (single rows that k_gemv holds in LDS)
 bool gemm_fuses_norm(int32_t M, int32_t K, const GemmB& B, int32_t N, int epilogue, bool have_ws);
 // true where launch_gemm_mfma has the fused epilogue (EPI_QKV_ROPE) for this QKV projection: up to 16 rows (k_gemv),
-// 8 to 128 (k_gemm_stream) and every launch on tiles.  That leaves 17 to 48 rows on the 4-bit form (k_gemm_skinny_w4), where the caller projects to
-// fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel, as it does for the token-granularity scheme.
+// 8 to 128 (k_gemm_stream) and every launch on tiles.  That leaves 17 rows and more on the 4-bit form (k_gemm_skinny_w4), where
+// the caller projects to fp32 (EPI_STORE_F32) and runs the RoPE/scatter kernel, as it does for the token-granularity scheme.
 bool gemm_mfma_fuses_qkv(int32_t M, int32_t K, const GemmB& B, int32_t N, bool have_ws);
 // bf16 expansion of an INT4 matrix: out[rows, K] = bf16((code - zero) * scale)
 void launch_dequant_int4(const void* codes, const void* scale_zero, int32_t rows, int32_t K, void* out, hipStream_t s);

@@ -79,6 +79,41 @@ def test_expansion_covers_every_code_zero_pair_and_awkward_scales():
     assert torch.equal(got.cpu().view(torch.int16), want.view(torch.int16))
 
 
+@pytest.mark.parametrize("hidden", [1024, 8192])
+def test_rows_around_the_line_of_the_4bit_form(hidden):
+    """33 rows and more run on the bf16 expansion, at hidden 8192 from 41: the same units with and without the 4-bit form
+    attached differ by the order of the sums alone (the bf16 launches are checked against the oracle at their sizes)."""
+    shape = ks.ModelShape(2, hidden, 2, 1, 128, hidden, 211, 1.0e6, 1e-6, "bf16")
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    layers, layers4 = [], []
+    for _ in range(2):
+        w, w4 = {}, {}
+        for name, (rows, k) in ((n, ks.layer_weight_shapes(shape)[n]) for n in ks.INT4_MATS):
+            codes = torch.randint(0, 256, (rows * k // 2,), generator=g, device="cuda", dtype=torch.uint8)
+            scale = torch.rand(rows * k // 128, generator=g, device="cuda").add_(0.5).mul_(0.2 / hidden ** 0.5)
+            words = (scale.to(torch.bfloat16).view(torch.int16).to(torch.int32) & 0xFFFF) | (8 << 16)
+            w4[name] = (codes, words.contiguous())
+            w[name] = dequantize_int4(*w4[name], rows, k)
+        for name, width in (("ln1", hidden), ("ln2", hidden), ("bq", 256), ("bk", 128), ("bv", 128)):
+            w[name] = torch.randn(width, generator=g, device="cuda").to(torch.bfloat16)
+        layers.append(w)
+        layers4.append(w4)
+    embed = (0.05 * torch.randn(211, hidden, generator=g, device="cuda")).to(torch.bfloat16)
+    plain, ctx = (KeepContext(shape, layers, embed, 64, 1) for _ in range(2))
+    ctx.attach_int4(layers4)
+    for n in (17, 32, 33, 40, 41, 48, 49):
+        ids = ks.make_token_ids(n, shape.vocab, n)
+        out = []
+        for c in (plain, ctx):
+            k, v = (torch.zeros((2, n, 1, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            c.precompute_group(ids, k, v)
+            out.append((k, v))
+        torch.cuda.synchronize()
+        for a, b in zip(*out):
+            assert max_rel(to_np(b), to_np(a)) < TOL / 2, n
+            assert torch.equal(a, b) == (n > (40 if hidden == 8192 else 32)), n
+
+
 def test_short_prompt_unit_caching_and_decode_read_the_int4_form():
     pb = Int4Problem(SHAPE)
     shape, sh, L = pb.shape, pb.sh, pb.shape.n_layers
@@ -89,7 +124,7 @@ def test_short_prompt_unit_caching_and_decode_read_the_int4_form():
     ctx = pb.context(cap, len(glen))
     plain = pb.context(cap, len(glen), int4=False)
 
-    # 1. caching memory units on their own: 36 rows (two row tiles per workgroup) and 30 rows (one)
+    # 1. caching memory units on their own: 36 rows (the bf16 expansion) and 30 rows (the 4-bit form)
     kb_d, vb_d = [[None] * len(glen) for _ in range(L)], [[None] * len(glen) for _ in range(L)]
     kb, vb = ko.precompute_group_caches(sh, pb.layers, pb.embed, ids, glen)
     off = 0
