@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(WM* WN * 64)
 //
 // (Inline assembly hides the products from the compiler's hazard checks.  Nothing but products may therefore touch an
 // accumulator before the wait behind the last one: the accumulators are read by get(), in assembly too, and the build
-// refuses a k_gemm_256 with scratch memory, where one might have been spilled right behind its product.)
+// refuses a k_gemm_256 with scratch memory, or with an instruction of the compiler's own that names an accumulator.)
 //
 // The weights are the A operand and the activations the B operand, and the weight rows of two neighbouring 16-row tiles
 // are dealt out alternately by fours: a lane then holds eight consecutive output columns of one row, and the epilogues
