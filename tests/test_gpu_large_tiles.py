@@ -1,13 +1,15 @@
 """The 256x256 tiles of the GEMM at the edges of a last tile's rows: more and fewer than 64, 128 and 192 of them, one, and
-none missing, through all four projections of a layer (the fused QKV epilogue with biases and unit-local positions, the
-residual add, SwiGLU) and the next layer's keys and values.  The same units cached one by one go through other kernels,
-which the oracle checks at their sizes; both round to bf16 at every step: 2e-2 of the largest value."""
+none missing: every projection of a layer for itself, where its tiles are whole and where they are cut along K (the fused
+QKV epilogue, the residual add and SwiGLU run inside the kernel in the one case, behind it in the other), and units
+with positions of their own, whose single passes go through other kernels; there both sides round to bf16 at every step:
+2e-2 of the largest value."""
 import numpy as np
 import pytest
 import torch
 
 import keep_synth as ks
 from gpu_util import Problem, max_rel, to_np
+from layer_probe import LayerProbe
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +67,27 @@ def test_hidden_rows_at_an_odd_address():
         torch.cuda.synchronize()
         outs.append(to_np(out) - to_np(x))
     assert np.isfinite(outs[0]).all() and max_rel(outs[1], outs[0]) < 2e-2
+
+
+EDGES = [2304 + e for e in (1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256)]
+
+
+def _cuts(rows, columns, k):
+    """Pieces along K of the last tiles of an XCD's share (1: whole), as the launch plans them."""
+    per_xcd = -(-(-(-rows // 256) * (columns // 256)) // 8)
+    rem = per_xcd % 32
+    return max(1, min(16, 32 // rem, k // 64 // 4)) if rem else 1
+
+
+# whole tiles: 13 columns of tiles for QKV, O and down (17 tiles per XCD: a second piece would not fit its 32 CUs); gate/up has
+# whole tiles and one per XCD that is cut.  Cut ones: 12, 10 and 10 columns of tiles.
+@pytest.mark.parametrize("heads,hidden,ffn,cuts", [(22, 3328, 3328, (1, 1, 13, 1)), (20, 2560, 4096, (2, 2, 4, 2))],
+                         ids=["whole", "cut"])
+def test_projections(heads, hidden, ffn, cuts):
+    shape = ks.ModelShape(1, hidden, heads, 2, 128, ffn, 211, 1.0e6, 1e-6, "bf16")
+    probe = LayerProbe(shape, EDGES[-1], seed=hidden)
+    for n in EDGES:
+        plan = tuple(_cuts(n, c, k) for c, k in ((shape.q_dim + 2 * shape.kv_dim, hidden), (hidden, shape.q_dim),
+                                                 (2 * ffn, hidden), (hidden, ffn)))
+        assert plan == cuts
+        probe.check(n)

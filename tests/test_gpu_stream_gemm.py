@@ -8,6 +8,7 @@ import torch
 
 import keep_synth as ks
 from gpu_util import Problem, max_rel, to_np
+from layer_probe import LayerProbe
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,26 @@ def test_units_match_oracle(shape, n):
             ek, ev = max_rel(to_np(kc[l][rows]), pb.kb[l][g]), max_rel(to_np(vc[l][rows]), pb.vb[l][g])
             print(n, "layer", l, "unit", g, "K %.2e V %.2e" % (ek, ev))
             assert ek < 2e-2 and ev < 2e-2
+
+
+# the same forms and edges, every projection of a layer for itself; and layers too wide for the oracle: weight rows a multiple
+# of 4 KB apart, where the workgroups start at different slices (gate/up at 2048, 4096, 6144; down 16384 x 6144 and QKV
+# 8192 x 10240, cut), the widest gate/up tiles (96 and 108 pairs of a workgroup) and, past 64 rows, two rounds of them
+BY_SHAPE = {}
+for _s, _n in NARROW + WIDE + FEW + CUT:
+    BY_SHAPE.setdefault((_s.hidden, _s.n_q_heads, _s.n_kv_heads, _s.ffn_dim), []).append(_n)
+BY_SHAPE[2048, 16, 4, 8192] = [8, 17, 32, 33, 64, 100, 128]
+BY_SHAPE[4096, 8, 2, 14336] = [8, 13, 16, 17, 48, 64, 65, 128]
+BY_SHAPE[4096, 2, 1, 24576] = [16, 17, 64, 65]
+BY_SHAPE[5120, 4, 1, 27648] = [16, 17, 64, 65, 128]
+BY_SHAPE[6144, 4, 1, 16384] = [8, 16, 17, 64, 65]
+BY_SHAPE[8192, 64, 8, 1024] = [8, 17, 33, 64, 65]
+
+
+@pytest.mark.parametrize("shape", BY_SHAPE, ids=lambda v: "h%d_q%d_f%d" % (v[0], v[1], v[3]))
+def test_projections(shape):
+    hidden, heads, kv, ffn = shape
+    rows = sorted(set(BY_SHAPE[shape]))
+    probe = LayerProbe(ks.ModelShape(1, hidden, heads, kv, 128, ffn, 211, 1.0e6, 1e-6, "bf16"), rows[-1], seed=ffn)
+    for n in rows:
+        probe.check(n)
