@@ -71,7 +71,7 @@ typedef enum { KEEP_LOAD_SERIAL = 0, KEEP_LOAD_NEXT_LAYER = 1, KEEP_LOAD_LAYER_B
 
 /* Kernel family.  AUTO: MFMA kernels when dtype is bf16 and head_dim is 128 and
  * hidden, ffn_dim are multiples of 64; otherwise the generic kernels.  GENERIC:
- * always the scalar-FMA kernels (any head_dim that is even, fp32 or bf16). */
+ * always the generic kernels (head_dim a multiple of 16 up to 256, fp32 or bf16). */
 typedef enum { KEEP_KERNELS_AUTO = 0, KEEP_KERNELS_GENERIC = 1 } keep_kernel_path;
 
 typedef struct {
@@ -148,7 +148,8 @@ typedef struct {
  * the FFN, Section 4.2 "System advantage") and host->device loading (Section 5,
  * the three pipelined threads).  All must be at the default priority.
  * Errors: INVALID_ARG (NULL, non-positive sizes, n_q_heads not a multiple of
- * n_kv_heads, odd head_dim), SHAPE (head_dim > 256, n_layers > 128, max_groups > 6000), HIP. */
+ * n_kv_heads), SHAPE (head_dim no multiple of 16 or > 256, hidden or ffn_dim no multiple of 8, n_layers > 128,
+ * max_groups > 6000), HIP. */
 keep_status keep_init(const keep_model_desc* desc, const keep_layer_weights* layers, const void* embed_table,
                       void* stream_compute, void* stream_eval, void* stream_copy, keep_ctx** out);
 
@@ -237,8 +238,9 @@ keep_status keep_select_groups(keep_ctx* ctx, const float* S, const int32_t* gro
 #define KEEP_STATIC_MAX_CANDIDATES 4096
 /* keep_select_groups for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It needs no context: the scratch that the selection uses
- * beyond its inputs and outputs (the candidates' lengths, their token total, the row totals of S) lives in a device
- * array built into the library (32.5 KiB, held by every GPU the library runs on until the process ends), and the call
+ * beyond its inputs and outputs (the candidates' lengths and token total, the row totals of S, importances and the set
+ * between launches) lives in a device array built into the library (96 KiB, held by every GPU the library runs on until
+ * the process ends), and the call
  * makes no allocation, on the device or through any library.  Inputs and outputs are DEVICE memory:
  *   S:         DEVICE [(n_sel + 1) * n_sel], last row the query (as keep_select_groups, but on the device).
  *   groups:    DEVICE [n_sel], strictly ascending group ids below n_groups_total (not checked; ids are clamped

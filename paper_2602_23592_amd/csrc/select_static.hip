@@ -1,8 +1,8 @@
 // keep_select_groups_static: the multi-hop selection for callers that cannot allocate.
 //
-// Same kernels as keep_select_groups (k_select_small; from 64 candidates on k_row_totals, k_select).  That entry point
-// keeps the candidates' lengths, their token total and the selection's scratch in the context's workspace (device memory
-// the library allocated at keep_init);
+// Same kernels as keep_select_groups (k_select_small; from 64 candidates on k_row_totals and k_select, from 900 on
+// k_select_step and k_propagate between them).  That entry point keeps the candidates' lengths, their token total and the
+// selection's scratch in the context's workspace (device memory the library allocated at keep_init);
 // here they live in a file-scope device array, so the call needs no context, no workspace and makes no
 // allocation of any kind.  Every GPU the library runs on holds its own copy of the array until the process
 // ends; all calls on one GPU share it, so calls that overlap on one GPU race.
