@@ -23,14 +23,19 @@ def _short(name):
     return name[:name.index("(")] if "(" in name else name
 
 
+def _only(d, name):
+    """The one file of this name under d.  Several are output of several runs, and none of them is picked."""
+    f = glob.glob(os.path.join(d, "**", "*" + name), recursive=True)
+    if len(f) != 1:
+        raise SystemExit("%d files *%s under %s, not one: give the output directory of a single run" % (len(f), name, d))
+    return f[0]
+
+
 def _counter_rows(d, after_calibration=True):
     """Rows of the counter CSV.  With after_calibration, only the dispatches that follow bench.py's calibration copy
     (--calib-copy-mib: the longest-running device-to-device copy), i.e. without the set-up launches (weights,
     group caches), but including that copy itself; the profiler cannot be paused in a --pmc run."""
-    f = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
-    if not f:
-        raise SystemExit("no counter_collection.csv under " + d)
-    rows = list(csv.DictReader(open(f[0])))
+    rows = list(csv.DictReader(open(_only(d, "counter_collection.csv"))))
     if after_calibration:
         copies = [r for r in rows if "copyBuffer" in r["Kernel_Name"]]
         if copies:
@@ -56,8 +61,7 @@ def _per_kernel(rows):
 
 def stats(argv):
     d, benchlog, out, cmd = argv
-    f = glob.glob(os.path.join(d, "**", "*kernel_stats.csv"), recursive=True)
-    rows = list(csv.DictReader(open(f[0])))
+    rows = list(csv.DictReader(open(_only(d, "kernel_stats.csv"))))
     bench = json.loads([l for l in open(benchlog) if l.startswith("{")][-1])
     with open(out, "w") as o:
         o.write("# rocprofv3 kernel stats: keep_prefill, %s (one MI355X)\n\n" % bench["config"]["workload"].split(":")[0])
