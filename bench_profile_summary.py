@@ -19,7 +19,7 @@ import time
 
 
 def _short(name):
-    name = name.replace("void keep::", "").replace("keep::", "")
+    name = name.replace("(anonymous namespace)::", "").replace("void keep::", "").replace("keep::", "")
     return name[:name.index("(")] if "(" in name else name
 
 

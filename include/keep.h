@@ -218,7 +218,8 @@ keep_status keep_recompute_layer(keep_ctx* ctx, const keep_prompt* prompt, int32
  *   groups[]; S[a, a] = 0.  Then: row-normalise, importance = query row, relevant set =
  *   top of the importance order within the budget, importance = mean of the normalised
  *   rows of the query and of the relevant set, repeat until the set repeats or `hops`
- *   selections were made (hops = 1: initialisation only).  Ties: lower group index.
+ *   selections were made (hops = 1: initialisation only; a set that alternates without repeating runs all of
+ *   them).  Ties: lower group index.
  *   ratio_next: share of the prompt's memories (or memory tokens) kept for the next layer.
  *   S_out: HOST [(n_sel+1) * n_sel] or NULL.  next_groups: HOST, capacity n_sel,
  *   ascending subset of groups[].  n_next, hops_run: HOST scalars.
