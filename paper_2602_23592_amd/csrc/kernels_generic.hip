@@ -546,32 +546,40 @@ __global__ void __launch_bounds__((ALONE ? SG_ALONE_WAVES : SG_WAVES) * 64)
   const int seen = own ? s0 : min(s_end, tc + 1);                      // ... this row
   float sum = 0.f;
   if (s0 < s1) {
-    const int tiles = (s1 - s0 + 15) / 16, items = n_q_heads * tiles;
-    int i = ALONE ? 0 : (int)((long)wave * items / SG_WAVES);
-    const int i_end = ALONE ? items : (int)((long)(wave + 1) * items / SG_WAVES);
-    int h = i / tiles, c = i - h * tiles, loaded = -1;
-    f32x4 qf[NT], kf[NT], kn[ALONE ? 1 : NT];
+    f32x4 qf[NT], kf[NT];
     float l = 0.f;
-    auto keys = [&](f32x4 (&v)[NT]) {
+    auto queries = [&](int h) {
+      load_head<NT>(q + ((size_t)tc * n_q_heads + h) * DH, kg, qf);
+      l = lse[(size_t)tc * n_q_heads + h];
+    };
+    auto keys = [&](int h, int c, f32x4 (&v)[NT]) {
       load_head<NT>(k_compact + (size_t)min(s0 + 16 * c + lq, s1 - 1) * kv_dim + (h / rep) * DH, kg, v);
     };
-    if (!ALONE && i < i_end) keys(kf);
-    for (; i < i_end; ++i) {
-      const int key0 = s0 + 16 * c + 4 * kg;  // the lane's four keys
-      if (h != loaded) {
-        load_head<NT>(q + ((size_t)tc * n_q_heads + h) * DH, kg, qf);
-        l = lse[(size_t)tc * n_q_heads + h];
-        loaded = h;
-      }
-      if constexpr (ALONE) keys(kf);
-      if (++c == tiles) c = 0, ++h;
-      if constexpr (!ALONE) {
-        if (i + 1 < i_end) keys(kn);
-      }
+    auto add = [&](int c) {
       const f32x4 d = dots<NT>(kf, qf);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sum += key0 + e < seen ? expf(d[e] * scale - l) : 0.f;
-      if constexpr (!ALONE) {
+      for (int e = 0; e < 4; ++e) sum += s0 + 16 * c + 4 * kg + e < seen ? expf(d[e] * scale - l) : 0.f;
+    };
+    const int tiles = (s1 - s0 + 15) / 16;
+    if constexpr (ALONE) {
+      for (int h = 0; h < n_q_heads; ++h) {
+        queries(h);
+        for (int c = 0; c < tiles; ++c) {
+          keys(h, c, kf);
+          add(c);
+        }
+      }
+    } else {
+      const int items = n_q_heads * tiles, i_end = (int)((long)(wave + 1) * items / SG_WAVES);
+      int i = (int)((long)wave * items / SG_WAVES), h = i / tiles, c = i - h * tiles, loaded = -1;
+      f32x4 kn[NT];
+      if (i < i_end) keys(h, c, kf);
+      for (; i < i_end; ++i) {
+        if (h != loaded) queries(loaded = h);
+        const int at = c;
+        if (++c == tiles) c = 0, ++h;
+        if (i + 1 < i_end) keys(h, c, kn);
+        add(at);
 #pragma unroll
         for (int u = 0; u < NT; ++u) kf[u] = kn[u];
       }
